@@ -933,19 +933,7 @@ extern "C" int kf_build(const kf_geometry* g, const kf_build_params* bp, const k
   A.queue = (int32_t*)ws;
   A.event_done = (int32_t*)((char*)ws + 256);
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(build_clear, dim3(1), dim3(256), 0, s, A.queue, A.event_done, hits->n_events, A.start_tick);
-  if (int rc = kf_check_launch()) return rc;
-  {
-    const int n_rows = hits->n_events * hits->n_layers * hits->n_z;
-    hipLaunchKernelGGL(fine_kernel, dim3((n_rows + 3) / 4), dim3(256), 0, s, n_rows, hits->n_phi, hits->n_z,
-                       hits->n_phi * refine, hits->offsets, hits->phi, (int32_t*)A.fine);
-    if (int rc = kf_check_launch()) return rc;
-    if (hits->n_hits > 0) {
-      hipLaunchKernelGGL(pack_kernel, dim3((hits->n_hits + 255) / 256), dim3(256), 0, s, hits->n_hits, hits->x,
-                         hits->y, hits->z, hits->phi, hits->cov, hits->orig, (float4*)A.hpack);
-      if (int rc = kf_check_launch()) return rc;
-    }
-  }
+  if (int rc = launch_prep(hits, refine, A.fine, A.hpack, A.queue, A.event_done, A.start_tick, s)) return rc;
   if (bp->arith == KF_ARITH_F64)
     return bp->state == 1
                ? (bp->window_mode == 1 ? launch<double, true, true>(A, lanes, bp->persistent_blocks, hist_waves, s)

@@ -877,18 +877,7 @@ extern "C" int kf_build_det(const kf_detector* d, const kf_build_params* bp, con
   A.counters = (unsigned long long*)ex.counters;
   A.queue = (int32_t*)ws;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(build_clear, dim3(1), dim3(256), 0, s, A.queue, (int32_t*)((char*)ws + 256), hits->n_events,
-                     (int64_t*)nullptr);
-  if (int rc = kf_check_launch()) return rc;
-  const int n_rows = hits->n_events * hits->n_layers * hits->n_z;
-  hipLaunchKernelGGL(fine_kernel, dim3((n_rows + 3) / 4), dim3(256), 0, s, n_rows, hits->n_phi, hits->n_z,
-                     hits->n_phi * refine, hits->offsets, hits->phi, (int32_t*)A.fine);
-  if (int rc = kf_check_launch()) return rc;
-  if (hits->n_hits > 0) {
-    hipLaunchKernelGGL(pack_kernel, dim3((hits->n_hits + 255) / 256), dim3(256), 0, s, hits->n_hits, hits->x, hits->y,
-                       hits->z, hits->phi, hits->cov, hits->orig, (float4*)A.hpack);
-    if (int rc = kf_check_launch()) return rc;
-  }
+  if (int rc = launch_prep(hits, refine, A.fine, A.hpack, A.queue, (int32_t*)((char*)ws + 256), nullptr, s)) return rc;
   return bp->arith == KF_ARITH_F64
              ? launch_det<double>(A, lanes, bp->persistent_blocks, hist_waves, s, &g_last_det_launch)
              : launch_det<float>(A, lanes, bp->persistent_blocks, hist_waves, s, &g_last_det_launch);
