@@ -8,18 +8,18 @@
 //
 // Per layer, per wave:
 //   1. every live slot predicts its candidate (FP32 or FP64 arithmetic);
-//   2. the search window is computed and the phi-sorted rows of the hit bins
-//      that cover it are scanned (binary search to the window's low edge,
-//      then a walk to its high edge); each in-window hit gets its chi2;
-//   3. each lane keeps its best cand_cap children in registers;
-//   4. the seed's children are merged across its S lanes, best first, by a
-//      64-bit rank key (nhits, chi2, parent slot, hit index) with lane
-//      shuffles; the winners take the slots 0..cap-1;
-//   5. the new slots pull the parent's predicted state by shuffles and apply
-//      the Kalman update with their hit;
+//   2. the search windows are computed and the hits in the phi-sorted rows of
+//      bins that cover them are tested, (candidate, hit) pairs shared by all
+//      lanes; wide windows only where a hit that can survive may lie;
+//   3. accepted hits go to a pool of their seed in LDS;
+//   4. the seed's children (hits and holes) are ranked by counting, best
+//      first by (nhits, chi2, parent slot, hit chi2, hit index); the best cap
+//      take the slots 0..cap-1;
+//   5. the new slots pull the parent's predicted state and apply the Kalman
+//      update with their hit;
 //   6. back-pointers (parent slot, hit) go to the wave's history table in the
-//      workspace; the best
-//      hit list is recovered at the end by walking it backwards.
+//      workspace; the best hit list is recovered at the end by walking it
+//      backwards.
 // Candidates with no child compete for a per-seed best-finished record (LDS).
 #include <stdint.h>
 #include <stdio.h>
@@ -33,6 +33,7 @@
 #include "kfwave.h"
 
 using namespace kfdev;
+using namespace kfreach;
 
 namespace {
 
@@ -97,6 +98,116 @@ template <typename T, typename U> __device__ inline U kv64(U v) {
   else return v;
 }
 
+// LDS accesses before and after stay in program order, also where one memory
+// is used with several types (a wave's LDS operations execute in order).
+__device__ inline void lds_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The bounds of a Reach over sorted positions [p0, p1): the packing chunks
+// that overlap them.
+__device__ inline void reach_bounds(const float4* pack, int n_hits, int p0, int p1, Reach& q) {
+  uint32_t l = 0, z = 0, lo = 0x7F800000u, hi = 0;
+  for (int c = p0 / kPackChunk; c * kPackChunk < p1; ++c) {
+    const uint32_t* w = (const uint32_t*)(pack + (size_t)c * kPackChunk * 3 + 2) + 3;
+    const uint32_t u = w[0], r = c * kPackChunk + 1 < n_hits ? w[12] : 0x7F80u;
+    l = (u & 0xFFFF0000u) > l ? (u & 0xFFFF0000u) : l;  // (non-negative floats order as integers)
+    z = (u & 0xFFFFu) > z ? (u & 0xFFFFu) : z;
+    lo = (r & 0xFFFF0000u) < lo ? (r & 0xFFFF0000u) : lo;
+    hi = (r & 0xFFFFu) > hi ? (r & 0xFFFFu) : hi;
+  }
+  q.v = l | z;
+  q.rad = lo | hi;
+}
+
+// The lanes of a candidate's seed.
+struct Group {
+  int sidx, base, slot, S;
+  bool used;
+};
+
+// A seed's accepted hits of a layer: a pool of kPoolPerCap * cap entries in
+// LDS, in no order (a candidate's own list is never needed: only the seed's
+// best cap children survive), and room for the holes of its candidates.
+//   e    [SEEDS][stride] {chi2, (slot << 24) | sorted position in the event}
+//   cnt  [SEEDS] entries
+//   seen [64] whether a candidate accepted a hit
+constexpr int kPoolPerCap = 7;  // (with the holes a seed has at most 8 cap <= 64 children)
+constexpr uint32_t kNoHit = 0xFFFFFFu;  // the position of a hole
+struct Pool {
+  uint2* e;
+  int32_t* cnt;
+  int32_t* seen;
+  int stride, full;
+};
+
+__device__ inline uint64_t readlane64(uint64_t v, int j) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, j);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), j);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// chi2 that a hit of the candidate may have to reach the seed's best cap,
+// `worst` the rank key of cap-th child known: such that the sum, rounded to
+// FP32, does not exceed the key's.
+template <typename T> __device__ inline float useful_chi2(uint64_t worst, T chi2, int nhits) {
+  const int n = 31 - (int)(worst >> 59);
+  const float sum = __uint_as_float((uint32_t)(worst >> 27));
+  if (nhits + 1 > n) return __builtin_inff();
+  return nhits + 1 < n ? -1.f : (float)((T)sum - chi2) + 1.3e-7f * sum;
+}
+
+// Cuts the pool of seed s (the same in every lane) to its best cap entries,
+// in rank order: one entry per lane (a pool holds at most 64), each ranked
+// against all others by the exact order of children (nhits, chi2, slot, hit
+// chi2, hit index).  Where more than cap entries were held, sets the chi2 bound
+// thr of the seed's candidates, and `cut`.
+template <typename T>
+__device__ inline void pool_cut(const BuildArgs& A, const Pool& po, const Group& gr, int s, int lane, T chi2, int nhits,
+                                int e0, float& thr, bool& cut) {
+  const int held = __builtin_amdgcn_readfirstlane(po.cnt[s]);
+  const int m = held < po.full ? held : po.full;
+  const bool in = lane < m;
+  uint2* pe = po.e + s * po.stride;
+  uint2 e = pe[in ? lane : 0];
+  const float c2 = __uint_as_float(e.x);
+  const int slot = in ? (int)(e.y >> 24) : 0, src = s * gr.S + slot;
+  const T pc = shfl_t(chi2, src);
+  const int pn = __shfl(nhits, src, 64), pe0 = __shfl(e0, src, 64);
+  const uint32_t orig =
+      in ? __float_as_uint(A.hpack[(size_t)(pe0 + (int)(e.y & 0xFFFFFFu)) * 3 + 2].z) : 0xFFFFFFFFu;
+  const uint64_t key = in ? make_key(pn + 1, (float)(pc + (T)c2), slot, 0) : kInfKey;
+  int rank = 0;
+  for (int i = 0; i < m; ++i) {
+    const uint64_t ki = readlane64(key, i);
+    const float ci = readlane_t(c2, i);
+    const uint32_t oi = (uint32_t)__builtin_amdgcn_readlane((int)orig, i);
+    rank += ki < key || (ki == key && top_before(ci, oi, c2, orig)) ? 1 : 0;
+  }
+  lds_order();
+  if (in && rank < A.cap) pe[rank] = e;
+  if (lane == 0) po.cnt[s] = m < A.cap ? m : A.cap;
+  lds_order();
+  if (m > A.cap) {
+    const uint64_t worst = readlane64(key, (int)__builtin_ctzll(__ballot(in && rank == A.cap - 1)));
+    if (gr.used && gr.sidx == s) {
+      thr = useful_chi2<T>(worst, chi2, nhits);
+      cut = true;
+    }
+  }
+}
+
+// A candidate is wide when its window may hold more than kWidePairs pairs;
+// it then first searches where its kProbeHits best hits should lie.
+#ifndef KF_WIDE_PAIRS
+#define KF_WIDE_PAIRS 128
+#endif
+#ifndef KF_PROBE_HITS
+#define KF_PROBE_HITS 20
+#endif
+constexpr float kWidePairs = KF_WIDE_PAIRS, kProbeHits = KF_PROBE_HITS;
+
 // Hit search of every candidate of the wave, shared by all 64 lanes.
 //
 // Each live candidate's window covers, per z row it overlaps and per phi
@@ -107,14 +218,25 @@ template <typename T, typename U> __device__ inline U kv64(U v) {
 // pairs per lane, so a candidate with a wide window no longer holds up the
 // wave while the others wait.  A lane finds the pair's candidate from the
 // marks the candidates set where their pairs start and reads what that
-// candidate's tests share by lane shuffles.  Every hit whose stored phi lies in the candidate's interval
-// gets the exact window test (z first, then the angle about the axis);
-// in-window hits get their chi2; accepted hits (chi2 < cut) are counted for
-// their candidate (a ballot over its run of lanes: a candidate's pairs occupy
-// consecutive lanes) and, if they can enter its list of the best cap (a full
-// list admits only hits that rank before its last entry), placed in it by
-// their ranks, all of the round's at once (round_insert).  The ranking is
-// total, so the result equals a serial scan.
+// candidate's tests share by lane shuffles.  Every hit whose stored phi lies
+// in the candidate's interval gets the exact window test (z first, then the
+// angle about the axis); in-window hits get their chi2; accepted hits
+// (chi2 < cut) go to their seed's pool (the slot from an LDS counter).  A
+// pool that is full is cut to its best cap entries, and from then on only
+// hits that can still be among them are added.
+//
+// Wide windows.  Few candidates hold most pairs (20 events of 20 000 tracks:
+// 0.04 % of the candidate-layers, their windows whole layers, half of all
+// pairs), and of all they accept only the seed's best cap children survive.
+// A wide candidate first searches where hits of chi2 <= c2 lie (Reach), c2
+// chosen to hold kProbeHits of them at the density of the window's middle
+// row.  The seed's pool then bounds the chi2 of a hit that can still be among
+// the survivors; where that bound is within c2 the search is complete, else
+// the seed is searched again up to the bound (or the chi2 cut).  What is left
+// out cannot survive; it would only have been counted, and the counts matter
+// to "any child" (known from the accepted hits or the hole) and to "cut to
+// cap" (known once the seed accepted more than cap).  Work counters ask for
+// every hit: no bound then.  Pairs, same events: 470 M -> 115 M.
 //
 // The tests and chi2 run in FP32 in both arithmetic modes, from the
 // prediction rounded to FP32: their rounding (chi2 ~ 3e-5 at the cut,
@@ -122,17 +244,22 @@ template <typename T, typename U> __device__ inline U kv64(U v) {
 // distances (1e-4 cm) that separate decisions; the Kalman update of a
 // chosen hit runs in the arithmetic of the mode.  NP (pairs per lane and
 // round at most) is defined with the LDS plan.
+//
+// seen: the candidate has a hit child; cut: the seed has more children than
+// cap; scanned, tested: work counters of the hits this lane examined.
 template <typename T, int NPT>
-__device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, const T Xp[6], const T Pp[21],
-                                 T dphi_w, T dz_w, TopList& tl, const AccBuf& ab, int lane) {
+__device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool pok, const T Xp[6], const T Pp[21],
+                                 T dphi_w, T dz_w, T chi2, int nhits, bool hole_ok, const Group& gr, const Pool& po,
+                                 int32_t* start, int lane, bool& seen, bool& cut, unsigned& scanned,
+                                 unsigned& tested) {
   static_assert(NPT >= 1 && NPT <= NP, "pairs per lane");
   const int nz = A.n_z, nf = A.n_phi * A.refine;
   const float inv = fine_inv(nf);
-  const float tp = 6.283185307179586f;
   // this lane's window as conservative stored-value intervals (the exact
-  // test decides): up to two phi intervals within [0, 2pi), z rows iz0..iz1
-  float a0 = 1.f, b0v = 0.f, a1 = 1.f, b1v = 0.f;
-  int iz0 = 0, iz1 = -1;
+  // test decides): a half-width hw about phip (3.14159 and more: the whole
+  // circle), z rows taken from the middle one outwards
+  float phip = 0.f, hw = 0.f;
+  Rows rw = {0, -1, 0};
   // Per candidate, what every hit test shares: for dphi < pi/2 the angle
   // test |atan2(cross, dot)| <= dphi is dot > 0 and |cross| <= tan(dphi) dot
   // (ftan < 0 marks a wider window, which keeps the angle); the measurement
@@ -141,26 +268,14 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, co
   float fx = 0.f, fy = 0.f, fz = 0.f, fdz = 0.f, fdphi = 0.f, ftan = 0.f;
   float firr = 0.f, suu = 0.f, suw = 0.f, sww = 0.f;
   if (pok) {
-    const float zh = A.z_half;
     fx = (float)Xp[0];
     fy = (float)Xp[1];
     fz = (float)Xp[2];
     fdz = (float)dz_w;
     fdphi = (float)dphi_w;
-    const float phip = wrap_2pi(atan2f(fy, fx));
-    const float eps_phi = 1e-5f, eps_z = 1e-4f;
-    const float dphi = fdphi + eps_phi, dz = fdz + eps_z;
-    iz0 = (int)floorf((fz - dz + zh) * (float)ku64<T>(A.n_z) / (2.f * zh));
-    iz1 = (int)floorf((fz + dz + zh) * (float)ku64<T>(A.n_z) / (2.f * zh));
-    iz0 = iz0 < 0 ? 0 : (iz0 > nz - 1 ? nz - 1 : iz0);
-    iz1 = iz1 < 0 ? 0 : (iz1 > nz - 1 ? nz - 1 : iz1);
-    if (dphi >= 3.14159f) { a0 = 0.f; b0v = tp; }
-    else {
-      const float lo = phip - dphi, hi = phip + dphi;
-      if (lo < 0.f) { a0 = 0.f; b0v = hi; a1 = lo + tp; b1v = tp; }
-      else if (hi >= tp) { a0 = lo; b0v = tp; a1 = 0.f; b1v = hi - tp; }
-      else { a0 = lo; b0v = hi; }
-    }
+    phip = wrap_2pi(atan2f(fy, fx));
+    hw = fdphi + kEpsPhi;
+    rw = rows_of(fz, fdz + kEpsZ, A.z_half, ku64<T>(A.n_z));
     // (the angle test runs in FP32: so does the tangent of its bound)
     ftan = !(dphi_w < T(1.5707963267948966)) ? -1.f : tanf((float)dphi_w);
     const T rr = k_sqrt(Xp[0] * Xp[0] + Xp[1] * Xp[1]);
@@ -172,19 +287,14 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, co
     sww = (float)Pp[ut(2, 2)];
   }
   const int32_t* frow = A.fine + ((size_t)ev * A.n_layers + l) * nz * (nf + 1);
-  // ranges: (row, interval) for every row, the second interval only where
-  // the window wraps at 2 pi
-  const int nint = a1 <= b1v ? 2 : 1;
-  const int R = pok ? (iz1 - iz0 + 1) * nint : 0;
-  const int Rmax = wave_max(R);
-  int n_acc = 0;  // accepted hits of this lane's candidate
-  int held = 0;           // entries in the list
-  bool unsorted = false;  // entries appended out of order
-  // the candidate's admission threshold: its last entry once its list is
-  // full (before, +inf admits every accepted hit)
-  float thr_c2 = __builtin_inff();
-  uint32_t thr_o = 0xFFFFFFFFu;
-  const float cut = A.chi2_cut;
+  // ranges: (row, interval) for every row, 1 << sh intervals per row (two
+  // where the window wraps at 2 pi, four of a Reach)
+  Reach rq = {0.f, 0u, 0u};
+  int sh = phi_parts(phip, hw);
+  int R = pok ? rw.n() << sh : 0;
+  const float chi2_cut = A.chi2_cut;
+  float thr = __builtin_inff();  // chi2 of a hit that may enter the pool
+  bool lim = false;              // any pool was cut: thr counts
   // range r of this candidate: its stored-value interval and its sorted
   // positions from the fine index (read one range ahead)
   auto range_of = [&](int r, float& a, float& b, int& q0, int& q1) {
@@ -193,25 +303,61 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, co
     q0 = 0;
     q1 = 0;
     if (r < R) {
-      const int ri = nint == 2 ? (r & 1) : 0, rr = nint == 2 ? (r >> 1) : r;
-      a = ri ? a1 : a0;
-      b = ri ? b1v : b0v;
+      const int row = rw.at(r >> sh), i = r & ((1 << sh) - 1);
+      if (sh == 2)
+        reach_part(rq, suu, suw, sww, k_sqrt(fx * fx + fy * fy), fz, phip, hw, fdz + kEpsZ, row, nz, A.z_half, i, a, b);
+      else
+        phi_part(phip, hw, i, a, b);
       if (a <= b) {
-        const int32_t* f = frow + (size_t)(iz0 + rr) * (nf + 1);
+        const int32_t* f = frow + (size_t)row * (nf + 1);
         q0 = f[fine_key(a, inv, nf)];
         q1 = f[fine_key(b, inv, nf) + 1];
       }
     }
   };
+  const int inv_s = 65536 / gr.S + 1;  // lane / S = lane * inv_s >> 16 (lanes < 64)
+  po.seen[lane] = 0;
+  if (gr.used && gr.slot == 0) po.cnt[gr.sidx] = 0;
 
   float an = 1.f, bn = 0.f;
   int p0n = 0, p1n = 0;
-  range_of(0, an, bn, p0n, p1n);
-  for (int r = 0; r < Rmax; ++r) {
+  bool wide = false, pruned = false;
+  float c2b = chi2_cut, del = 0.f;
+  bool look = A.counters == nullptr;  // wide windows still to be looked for
+  bool again = false;                 // a wide candidate's bound still to be checked
+  int Rmax = wave_max(R);
+  // (one call of range_of in the code: the pass over the ranges starts one
+  // before the first, where only the first is read)
+  for (int r = -1;;) {
     const float a = an, b = bn;
     const int p0 = p0n, p1 = p1n;
     range_of(r + 1, an, bn, p0n, p1n);
-    const int cnt = p1 > p0 ? p1 - p0 : 0;
+    if (r < 0 && look) {
+      look = false;
+      const int c0 = p1n - p0n;  // the middle row
+      wide = pok && (float)c0 * (float)rw.n() > kWidePairs;
+      if (__any(wide)) {
+        if (wide) {
+          const int32_t* of = A.offsets + ((size_t)ev * A.n_layers + l) * ((size_t)A.n_phi * nz + 1);
+          reach_bounds(A.hpack, A.n_hits, of[rw.lo * A.n_phi], of[(rw.hi + 1) * A.n_phi], rq);
+          del = reach_del(rq, suu, suw, sww);
+          wide = del > 0.f;
+          if (wide) {
+            const float area = 4.f * fminf(hw, 3.1415927f) * k_sqrt(fx * fx + fy * fy) * A.z_half / (float)nz;
+            const float s2 = (suu + rq.lam()) * (sww + rq.vzz()) - suw * suw;
+            c2b = fminf(kProbeHits * area / (3.1415927f * k_sqrt(s2) * (float)c0), chi2_cut);
+            rq.c2 = c2b * reach_margin(del);
+            rw = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
+            sh = 2;
+            R = rw.n() << sh;
+          }
+        }
+        again = __any(wide && c2b < chi2_cut);
+        Rmax = wave_max(R);
+        continue;
+      }
+    }
+    const int cnt = r >= 0 && p1 > p0 ? p1 - p0 : 0;
     int total = 0;
     const int off = wave_excl_scan(cnt, lane, total);
     const int pb = p0 - off;  // sorted position of pair k of this candidate: pb + k
@@ -223,24 +369,20 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, co
       // in this round; the pair's candidate is the nearest mark at or below
       // its slot in its half, else the one whose pairs run on from before
 #pragma unroll
-      for (int h = 0; h < NPT; ++h) ab.start[h * 64 + lane] = -1;
-      if (cnt > 0 && off >= base && off - base < 64 * NPT) ab.start[off - base] = lane;
-      __builtin_amdgcn_wave_barrier();
-      int c[NPT], my_lo[NPT], p[NPT];
-      unsigned long long sma[NPT];  // the half's marks
+      for (int h = 0; h < NPT; ++h) start[h * 64 + lane] = -1;
+      if (cnt > 0 && off >= base && off - base < 64 * NPT) start[off - base] = lane;
+      lds_order();
+      int c[NPT], p[NPT];
       bool valid[NPT];
       float ca[NPT], cb[NPT], cx[NPT], cy[NPT], cz[NPT], cdz[NPT], cdphi[NPT], ctan[NPT], cirr[NPT], csuu[NPT], csuw[NPT],
-          csww[NPT], cthr[NPT];
-      uint32_t cthro[NPT];
+          csww[NPT];
 #pragma unroll
       for (int h = 0; h < NPT; ++h) {
-        const int st = ab.start[h * 64 + lane];
-        sma[h] = __ballot(st >= 0);
-        const unsigned long long sm = sma[h] & ((2ull << lane) - 1ull);
+        const int st = start[h * 64 + lane];
+        const unsigned long long sm = __ballot(st >= 0) & ((2ull << lane) - 1ull);
         const int hb = sm ? 63 - (int)__builtin_clzll(sm) : 0;
         const int sc = __shfl(st, hb, 64);
         c[h] = sm ? sc : carry;
-        my_lo[h] = sm ? hb : 0;  // first slot of this pair's candidate in the half
         carry = __builtin_amdgcn_readlane(c[h], 63);
         const int k = base + 64 * h + lane;
         valid[h] = k < total;
@@ -257,13 +399,10 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, co
         csuu[h] = __shfl(suu, c[h], 64);
         csuw[h] = __shfl(suw, c[h], 64);
         csww[h] = __shfl(sww, c[h], 64);
-        cthr[h] = __shfl(thr_c2, c[h], 64);
-        cthro[h] = (uint32_t)__shfl((int)thr_o, c[h], 64);
       }
       // everything each pair can need, in one round trip for all NP pairs
       // (a pair past the end reads the round's first pair, which exists)
       float ph[NPT], hx[NPT], hy[NPT], hz[NPT], V[NPT][6];
-      uint32_t forig[NPT];
       const int p_first = __builtin_amdgcn_readfirstlane(__shfl(p[0], 0, 64));
 #pragma unroll
       for (int h = 0; h < NPT; ++h) {
@@ -280,31 +419,27 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, co
         V[h][3] = u1.w;
         V[h][4] = u2.x;
         V[h][5] = u2.y;
-        forig[h] = __float_as_uint(u2.z);
       }
       // all loads in flight before the first test (the compiler would
       // otherwise wait for phi and issue the rest behind the phi test)
 #pragma unroll
       for (int h = 0; h < NPT; ++h)
         asm volatile("" ::"v"(ph[h]), "v"(hx[h]), "v"(hy[h]), "v"(hz[h]), "v"(V[h][0]), "v"(V[h][1]), "v"(V[h][2]),
-                     "v"(V[h][3]), "v"(V[h][4]), "v"(V[h][5]), "v"(forig[h]));
-      bool keep[NPT], acc[NPT];
+                     "v"(V[h][3]), "v"(V[h][4]), "v"(V[h][5]));
+      bool acc[NPT];
       float c2[NPT];
-      uint32_t orig[NPT];
 #pragma unroll
       for (int h = 0; h < NPT; ++h) {
-        keep[h] = false;
         acc[h] = false;
         c2[h] = 0.f;
-        orig[h] = 0;
         if (valid[h] && ph[h] >= ca[h] && ph[h] <= cb[h]) {
-          tl.scanned += 1;
+          scanned += 1;
           const float cr = cx[h] * hy[h] - cy[h] * hx[h], dt = cx[h] * hx[h] + cy[h] * hy[h];
           const bool in_phi =
               ctan[h] < 0.f ? fabsf(atan2f(cr, dt)) <= cdphi[h] : (dt > 0.f && fabsf(cr) <= ctan[h] * dt);
           if (fabsf(hz[h] - cz[h]) <= cdz[h] && in_phi) {
             // innovation in the tangent-plane frame and its chi2 (2 dof)
-            tl.tested += 1;
+            tested += 1;
             const float ctx = -cy[h] * cirr[h], cty = cx[h] * cirr[h];
             const float r0 = ctx * (hx[h] - cx[h]) + cty * (hy[h] - cy[h]), r1 = hz[h] - cz[h];
             const float s00 = csuu[h] + ctx * ctx * V[h][0] + 2.f * ctx * cty * V[h][1] + cty * cty * V[h][3];
@@ -314,43 +449,173 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int l, bool pok, co
             if (s00 > 0.f && det > 0.f) {
               // (the hardware reciprocal: within a few ulp, no division sequence)
               c2[h] = (s11 * r0 * r0 - 2.f * s01 * r0 * r1 + s00 * r1 * r1) * k_rcp(det);
-              if (c2[h] < cut) {
-                acc[h] = true;
-                orig[h] = forig[h];
-                keep[h] = top_before(c2[h], orig[h], cthr[h], cthro[h]);
-              }
+              acc[h] = c2[h] < chi2_cut;
             }
           }
         }
       }
-      // the admissible hits of each half enter their candidates' lists
+      // the accepted hits of each half into their seeds' pools
 #pragma unroll
       for (int h = 0; h < NPT; ++h) {
-        // this lane's run as a candidate in the half: lanes [s0, e0)
-        const int bh = base + 64 * h;
-        const int s0 = off - bh > 0 ? off - bh : 0;
-        const int e0 = off + cnt - bh < 64 ? off + cnt - bh : 64;
-        // accepted hits of each candidate: the accepted lanes of its run
-        const unsigned long long am = __ballot(acc[h]);
-        if (s0 < e0) n_acc += __builtin_popcountll(am & run_mask(s0, e0));
-        const unsigned long long m = __ballot(keep[h]);
-        if (m) {
-          // the run of this lane's pair: from its candidate's mark to the next
-          const unsigned long long above = sma[h] & ~((2ull << lane) - 1ull);
-          const int rhi = above ? (int)__builtin_ctzll(above) : 64;
-          round_insert(tl, A.cap, lane, m, keep[h], c2[h], p[h], orig[h], c[h], my_lo[h], rhi, s0, e0, held, unsorted,
-                       thr_c2, thr_o, ab.pub_c2, ab.pub_o);
+        if (!__any(acc[h])) continue;
+        if (acc[h]) po.seen[c[h]] = 1;
+        const int sd = c[h] * inv_s >> 16;
+        const uint32_t ref = ((uint32_t)(c[h] - sd * gr.S) << 24) | (uint32_t)(p[h] - __shfl(e0, c[h], 64));
+        bool pend = acc[h];
+        if (lim) {  // (the shuffle by all lanes)
+          const float ct = __shfl(thr, c[h], 64);
+          pend = pend && c2[h] <= ct;
+        }
+        for (;;) {
+          if (pend) {
+            const int i = atomicAdd(&po.cnt[sd], 1);
+            if (i < po.full) {
+              po.e[sd * po.stride + i] = make_uint2(__float_as_uint(c2[h]), ref);
+              pend = false;
+            }
+          }
+          const unsigned long long pm = __ballot(pend);
+          if (!pm) break;
+          pool_cut<T>(A, po, gr, __builtin_amdgcn_readlane(sd, (int)__builtin_ctzll(pm)), lane, chi2, nhits, e0, thr, cut);
+          lim = true;
+          const float ct = __shfl(thr, c[h], 64);
+          pend = pend && c2[h] <= ct;
         }
       }
     }
+    if (++r < Rmax) continue;
+    if (!again) break;
+    // the bounds of the wide candidates
+    again = false;
+    unsigned long long wm = __ballot(wide && c2b < chi2_cut);
+    unsigned long long redo = 0ull;  // lanes of the seeds to be searched again
+    const unsigned long long gm = ((1ull << gr.S) - 1ull);
+    while (wm) {
+      const int s = __builtin_amdgcn_readlane(gr.sidx, (int)__builtin_ctzll(wm));
+      const unsigned long long sm = gm << (s * gr.S);
+      wm &= ~sm;
+      pool_cut<T>(A, po, gr, s, lane, chi2, nhits, e0, thr, cut);
+      lim = true;
+      bool miss = false;
+      if (gr.sidx == s && wide && c2b < chi2_cut) {
+        pruned = cut && thr < chi2_cut && (po.seen[lane] != 0 || hole_ok);
+        miss = !pruned || thr > c2b;
+        if (miss) c2b = pruned ? thr : chi2_cut;
+      }
+      if (__any(miss)) redo |= sm;
+    }
+    R = 0;
+    if (!redo) break;
+    if (redo >> lane & 1ull) {
+      if (gr.slot == 0) po.cnt[gr.sidx] = 0;
+      if (!pruned) po.seen[lane] = 0;
+      if (wide) {
+        rq.c2 = c2b * reach_margin(del);
+        rw = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
+      }
+      R = pok ? rw.n() << sh : 0;
+    }
+    Rmax = wave_max(R);
+    r = -1;
   }
-  if (unsorted) sort_own(tl, A.cap, held);
-  tl.n = held;
   __builtin_amdgcn_s_waitcnt(0);
-  __builtin_amdgcn_wave_barrier();
-  tl.tot = n_acc;
+  lds_order();
+  seen = po.seen[lane] != 0;
 }
 
+// The seeds' best cap children (section 4.3): pool entries and holes ranked
+// by one pass of comparisons.  Every child gets a 64-bit key (nhits, chi2,
+// slot as in make_key, then the upper bits of its hit's chi2 and its place in
+// the pool); lane `slot` of a seed takes every S-th child of the seed, counts
+// the keys below each, and places those within the best cap + 1 in win.
+// Keys that differ only in the place are a tie the key cannot order: such a
+// seed's pool is put in exact order (pool_cut) and ranked again, where the
+// place decides.  keys: [SEEDS][stride] u64, win: [SEEDS][cap + 1] u64.
+//
+// Ranking against every child of the seed costs some 2 instructions per
+// comparison and no chain of dependent steps; popping the best of the
+// candidates' sorted lists cap times was a chain of cap times three shuffle
+// round trips and an LDS read (8 800 of a layer's 49 000 cycles, beside 2 500
+// for sorting the lists and 8 500 for keeping them sorted).
+// With the bounded search: 20 events of 20 000 tracks, build kernel FP64
+// 8.87 -> 4.96 ms, FP32 one event 3.69 -> 1.99 ms (20 000 tracks, its slowest
+// wave).
+//
+// Returns the number of children kept; n_all: children before the cut.
+template <int NI>
+__device__ inline void rank_items(const uint64_t* kv, const uint64_t* key, int* rank, int m, int mmax) {
+  for (int i = 0; i < mmax; ++i) {
+    uint64_t k = kv[i];
+    k = i < m ? k : kInfKey;
+#pragma unroll
+    for (int t = 0; t < NI; ++t) rank[t] += k < key[t] ? 1 : 0;
+  }
+}
+template <typename T>
+__device__ inline int best_children(const BuildArgs& A, const Pool& po, const Group& gr, uint64_t* keys, uint64_t* win,
+                                    int lane, T chi2, int nhits, int e0, bool hole_ok, bool& cut, uint2& child) {
+  constexpr int NT = kPoolPerCap + 1;
+  const int cap = A.cap, S = gr.S, sx = gr.used ? gr.sidx : 0;
+  const unsigned long long gm = ((1ull << S) - 1ull) << gr.base;
+  const unsigned long long hm = __ballot(hole_ok && gr.used) & gm;
+  uint2* pe = po.e + sx * po.stride;
+  uint64_t* kv = keys + sx * po.stride;
+  uint64_t* wv = win + sx * (cap + 1);
+  for (bool exact = false;;) {
+    const int held = po.cnt[sx], m0 = held < po.full ? held : po.full;
+    const int m = gr.used ? m0 + __builtin_popcountll(hm) : 0;
+    if (hole_ok && gr.used)
+      pe[m0 + __builtin_popcountll(hm & ((1ull << lane) - 1ull))] = make_uint2(0u, ((uint32_t)gr.slot << 24) | kNoHit);
+    lds_order();
+    const int mmax = wave_max(m);
+    uint64_t key[NT];
+    int rank[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      key[t] = kInfKey;
+      rank[t] = 0;
+      if (t * S < mmax) {
+        const int j = gr.slot + t * S;
+        const bool in = gr.used && j < m;
+        const uint2 e = pe[in ? j : 0];
+        const int src = gr.base + (in ? (int)(e.y >> 24) : gr.slot);
+        const T pc = shfl_t(chi2, src);
+        const int pn = __shfl(nhits, src, 64);
+        const bool hit = (e.y & 0xFFFFFFu) != kNoHit;
+        const float c2 = __uint_as_float(e.x);
+        if (in) {
+          key[t] = ((uint64_t)(31 - pn - (hit ? 1 : 0)) << 59) | ((uint64_t)chi2_bits((float)(pc + (T)c2)) << 28) |
+                   ((uint64_t)(e.y >> 24) << 25) | ((uint64_t)(chi2_bits(c2) >> 12) << 6) | (uint64_t)j;
+          kv[j] = key[t];
+        }
+      }
+    }
+    lds_order();
+    if (mmax <= 2 * S) rank_items<2>(kv, key, rank, m, mmax);
+    else if (mmax <= 4 * S) rank_items<4>(kv, key, rank, m, mmax);
+    else rank_items<NT>(kv, key, rank, m, mmax);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t * S < mmax && key[t] != kInfKey && rank[t] <= cap) wv[rank[t]] = key[t];
+    lds_order();
+    const bool kept = gr.used && gr.slot < m;  // (slot < cap)
+    const uint64_t k0 = wv[kept ? gr.slot : 0];
+    const bool tie = kept && gr.slot + 1 < m && (k0 >> 6) == (wv[kept ? gr.slot + 1 : 0] >> 6);
+    unsigned long long tm = exact ? 0ull : __ballot(tie);
+    if (!tm) {
+      child = pe[kept ? (int)(k0 & 63) : 0];
+      cut = cut || m > cap;
+      return m < cap ? m : cap;
+    }
+    while (tm) {
+      const int s = __builtin_amdgcn_readlane(gr.sidx, (int)__builtin_ctzll(tm));
+      tm &= ~(((1ull << S) - 1ull) << (s * S));
+      float thr;
+      pool_cut<T>(A, po, gr, s, lane, chi2, nhits, e0, thr, cut);
+    }
+    exact = true;
+  }
+}
 
 // Waves per SIMD the register allocation aims at.  The build waits on
 // memory and LDS most of the time, so a second resident wave pays even where
@@ -397,23 +662,35 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
   // this wave's back-pointer table (written once per new candidate and layer,
   // read once per seed at the end)
   uint32_t* hist = A.hist + ((size_t)blockIdx.x * nwaves + wave) * LB * 64;
-  float* stash = (float*)(base + lp.stash) + (size_t)wave * (XS ? 21 - NPL : 27) * 64;
-  T* xs = (T*)(base + lp.xs) + (size_t)wave * (XS ? 6 + NPL : 0) * 64 + lane;
+  // the state before a layer's prediction, in the output precision, for the
+  // finished record: entry k of 27 (the stash, then the first half of xs);
+  // after the records of a layer the same memory holds the children's keys
+  constexpr int NST = XS ? 21 - NPL : 27, NX2 = XS ? 6 + NPL : 0;
+  float* stash = (float*)(base + lp.stash) + (size_t)wave * NST * 64;
+  T* xs = (T*)(base + lp.xs) + (size_t)wave * NX2 * 64;
+  auto before = [&](int k) -> float& { return k < NST ? stash[k * 64 + lane] : ((float*)xs)[(k - NST) * 64 + lane]; };
+  uint64_t* keys = XS && !LEARNED ? (uint64_t*)xs : (uint64_t*)stash;
+  uint64_t* win = !XS || HYB ? (LEARNED && XS ? (uint64_t*)xs : keys + 512) : (LEARNED ? (uint64_t*)xs : (uint64_t*)stash);
+  // the last NXL covariance entries of the prediction, in FP64 builds kept in
+  // the second half of xs during the hit search
+  constexpr int NXL = NX2 / 2;
+  T* xp = xs + NXL * 64;
   float* fin = (float*)(base + lp.rec) + (size_t)wave * SEEDS * 27;
   int32_t* finm = (int32_t*)(base + lp.recf) + (size_t)wave * SEEDS * 5;
-  // per wave: the network buffer, or (after the network has run) the toplists
+  // per wave: the network buffer, or (after the network has run) the pools
   char* wave_tl = base + lp.tl + (size_t)wave * lp.tl_stride;
   uint16_t* mlp_buf = (uint16_t*)wave_tl;
-  float* tl_c2 = (float*)wave_tl + lane;
-  int32_t* tl_pos = (int32_t*)(wave_tl + (size_t)S * 64 * 4) + lane;
-  uint32_t* tl_orig = (uint32_t*)(wave_tl + (size_t)S * 64 * 8) + lane;
-  AccBuf ab;
-  ab.start = (int32_t*)(base + lp.acc) + (size_t)wave * 64 * NP;
-  ab.pub_c2 = (float*)(base + lp.pub) + (size_t)wave * 128;
-  ab.pub_o = (uint32_t*)ab.pub_c2 + 64;
+  Pool po;
+  po.e = (uint2*)wave_tl;
+  po.cnt = (int32_t*)(base + lp.pub) + (size_t)wave * 128;
+  po.seen = po.cnt + 64;
+  po.stride = (kPoolPerCap + 1) * S;
+  po.full = kPoolPerCap * S;
+  int32_t* start = (int32_t*)(base + lp.acc) + (size_t)wave * 64 * NP;
   (void)mlp_buf;
   const int sidx = lane / S, slot = lane - (lane / S) * S, sbase = sidx * S;
   const bool lane_used = sidx < SEEDS;
+  const Group gr = {sidx, sbase, slot, S, lane_used};
 
   if (A.start_tick && lane == 0) atomicMin((unsigned long long*)A.start_tick, (unsigned long long)wall_clock64());
 
@@ -429,6 +706,8 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
     const bool seed_ok = seed >= 0 && seed < A.n_seeds && ev >= 0 && ev < A.n_events;
     if (!seed_ok) { seed = 0; ev = 0; }
     const int q = seed_ok ? A.q[seed] : 1;
+    // first sorted position of the event
+    const int e0 = A.offsets[(size_t)ev * A.n_layers * ((size_t)A.n_phi * A.n_z + 1)];
     // candidate state
     T X[6], P[21];
 #pragma unroll
@@ -465,12 +744,6 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
       }
       n_active = 0;
     }
-    if constexpr (XS) {
-#pragma unroll
-      for (int k = 0; k < 6; ++k) xs[k * 64] = X[k];
-#pragma unroll
-      for (int k = 0; k < NPL; ++k) xs[(6 + k) * 64] = P[21 - NPL + k];
-    }
     T fin_chi2_reg = 0;  // chi2 of the finished record, kept by slot 0 of the seed
     unsigned cnt_pred = 0, cnt_scan = 0, cnt_chi2 = 0, cnt_upd = 0;
     int last_l = A.first_layer - 1;
@@ -479,25 +752,11 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
       if (!__any(n_active > 0)) break;
       last_l = l;
       const bool live = slot < n_active;
-      if constexpr (XS) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) X[k] = xs[k * 64];
-#pragma unroll
-        for (int k = 0; k < NPL; ++k) P[21 - NPL + k] = xs[(6 + k) * 64];
-      }
-      // the state before prediction is kept (in the output precision) for
-      // the finished record, so it need not stay in registers (the part held
-      // in LDS is read from there)
       if (live) {
-        if constexpr (XS) {
 #pragma unroll
-          for (int k = 0; k < 21 - NPL; ++k) stash[k * 64 + lane] = (float)P[k];
-        } else {
+        for (int k = 0; k < 6; ++k) before(k) = (float)X[k];
 #pragma unroll
-          for (int k = 0; k < 6; ++k) stash[k * 64 + lane] = (float)X[k];
-#pragma unroll
-          for (int k = 0; k < 21; ++k) stash[(6 + k) * 64 + lane] = (float)P[k];
-        }
+        for (int k = 0; k < 21; ++k) before(6 + k) = (float)P[k];
       }
       T Xp[6], Pp[21];
       int rc = 1;
@@ -516,14 +775,6 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
         for (int k = 0; k < 21; ++k) Pp[k] = T(0);
       }
       const bool pok = live && rc == 0;
-      TopList tl;
-      tl.c2 = tl_c2;
-      tl.pos = tl_pos;
-      tl.orig = tl_orig;
-      tl.n = 0;
-      tl.tot = 0;
-      tl.scanned = 0;
-      tl.tested = 0;
       // plain window from the predicted covariance
       T w_rphi = T(0), w_z = T(0);
       const T R = (T)A.r[l];
@@ -606,34 +857,32 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
         }
       }
       const T dphi_w = pok ? w_rphi / R : T(0), dz_w = pok ? w_z : T(0);
-      coop_scan<T, NPT_OF<T, LEARNED>>(A, kv64<T>(ev), l, pok, Xp, Pp, dphi_w, dz_w, tl, ab, lane);
       const bool hole_ok = pok && holes < A.max_holes;
-      const int nchild = tl.tot + (hole_ok ? 1 : 0);
+      bool seen = false, cut = false;
+#pragma unroll
+      for (int k = 0; k < NXL; ++k) xp[k * 64 + lane] = Pp[21 - NXL + k];
+      coop_scan<T, NPT_OF<T, LEARNED>>(A, kv64<T>(ev), e0, l, pok, Xp, Pp, dphi_w, dz_w, chi2, nhits, hole_ok, gr, po,
+                                       start, lane, seen, cut, cnt_scan, cnt_chi2);
+      const int nchild = (seen ? 1 : 0) + (hole_ok ? 1 : 0);
       // finished candidates of this layer (live, no child) compete for the record
       if (__any(live && nchild == 0)) {  // (most layers have none)
         const bool stopped = live && nchild == 0;
         uint64_t fk = stopped ? make_key(nhits, (float)chi2, slot, 0) : kInfKey;
         const uint64_t best = group_min(fk, sbase, slot, S, lane_used);
+        const int ws = (int)((best >> 24) & 7);
+        const int wl_ = sbase + ws;
+        // winner's chi2 in T and its fields
+        const T wc2 = shfl_t(chi2, wl_);
+        const int wn = __shfl(nhits, wl_, 64);
+        const int wst = __shfl(live && rc ? rc : 0, wl_, 64);
+        const T fc2 = shfl_t(fin_chi2_reg, sbase);
         if (best != kInfKey) {
-          const int ws = (int)((best >> 24) & 7);
-          const int wl_ = sbase + ws;
-          // winner's chi2 in T and its fields
-          const T wc2 = shfl_t(chi2, wl_);
-          const int wn = __shfl(nhits, wl_, 64);
-          const int wst = __shfl(live && rc ? rc : 0, wl_, 64);
           const int fvalid = finm[sidx * 5 + 0];
           const int fn = finm[sidx * 5 + 1];
-          const T fc2 = shfl_t(fin_chi2_reg, sbase);
           const bool take = !fvalid || wn > fn || (wn == fn && wc2 < fc2);
           if (take) {
             if (slot == ws) {
-              if constexpr (XS) {
-                for (int k = 0; k < 6; ++k) fin[sidx * 27 + k] = (float)xs[k * 64];
-                for (int k = 0; k < 21 - NPL; ++k) fin[sidx * 27 + 6 + k] = stash[k * 64 + lane];
-                for (int k = 21 - NPL; k < 21; ++k) fin[sidx * 27 + 6 + k] = (float)xs[(6 + k - 21 + NPL) * 64];
-              } else {
-                for (int k = 0; k < 27; ++k) fin[sidx * 27 + k] = stash[k * 64 + lane];
-              }
+              for (int k = 0; k < 27; ++k) fin[sidx * 27 + k] = before(k);
               finm[sidx * 5 + 0] = 1; finm[sidx * 5 + 1] = wn; finm[sidx * 5 + 2] = wst;
               finm[sidx * 5 + 3] = l - 1; finm[sidx * 5 + 4] = ws;
             }
@@ -641,85 +890,38 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
           }
         }
       }
-      // merge the children of the seed, best first, into slots 0..cap-1
-      int ptr = 0;
-      bool hole_left = hole_ok;
-      int my_parent = -1, my_pos = -1;
-      uint32_t my_orig = kHoleIdx;
-      T my_c2 = 0;
-      int n_new = 0;
-      for (int r = 0; r < A.cap; ++r) {
-        uint64_t key = kInfKey;
-        float hc2 = 0.f;
-        int hpos = -1;
-        uint32_t horig = kHoleIdx;
-        if (pok) {
-          if (ptr < tl.n) {
-            top_get(tl, ptr, hc2, hpos, horig);
-            key = make_key(nhits + 1, (float)(chi2 + (T)hc2), slot, horig);
-          } else if (hole_left) {
-            key = make_key(nhits, (float)chi2, slot, kHoleIdx);
-          }
-        }
-        const uint64_t win = group_min(key, sbase, slot, S, lane_used);
-        if (win == kInfKey) continue;  // no more children for this seed
-        const int ws = (int)((win >> 24) & 7);
-        const int wl_ = sbase + ws;
-        const int wpos = __shfl(hpos, wl_, 64);
-        const T wc2 = (T)__shfl(hc2, wl_, 64);
-        if (slot == ws) {
-          if (ptr < tl.n) ptr += 1; else hole_left = false;
-        }
-        if (slot == r) {
-          my_parent = ws;
-          my_pos = wpos;
-          my_orig = (uint32_t)(win & 0xFFFFFFu);
-          my_c2 = wc2;
-        }
-        n_new = r + 1;
-      }
-      // children left after cap rounds (accepted hits beyond a full list
-      // included): the seed's candidates were cut to cap
-      {
-        const bool left = pok && tl.tot - ptr + (hole_left ? 1 : 0) > 0;
-        const unsigned long long lm = __ballot(left);
-        if (lane_used && ((lm >> sbase) & ((1ull << S) - 1ull)) != 0ull) seed_status |= KF_CAP_TRUNC;
-      }
+      // the seed's best children into slots 0..cap-1
+      lds_order();
+      uint2 child;
+      const int n_new =
+          best_children<T>(A, po, gr, keys, win, lane, chi2, nhits, e0, hole_ok, cut, child);
+      const bool is_hole = (child.y & 0xFFFFFFu) == kNoHit;
+      const int my_parent = lane_used && slot < n_new ? (int)(child.y >> 24) : -1;
+      if (lane_used && cut) seed_status |= KF_CAP_TRUNC;
       // new slots pull the parent's predicted state
       const int src = sbase + (my_parent >= 0 ? my_parent : slot);
-      T Xn[6], Pn[21];
 #pragma unroll
-      for (int k = 0; k < 6; ++k) Xn[k] = shfl_t(Xp[k], src);
+      for (int k = 0; k < 6; ++k) X[k] = shfl_t(Xp[k], src);
 #pragma unroll
-      for (int k = 0; k < 21; ++k) Pn[k] = shfl_t(Pp[k], src);
+      for (int k = 0; k < 21; ++k) P[k] = k < 21 - NXL ? shfl_t(Pp[k], src) : xp[(k - 21 + NXL) * 64 + src];
       const T pchi2 = shfl_t(chi2, src);
       const int pnh = __shfl(nhits, src, 64), pho = __shfl(holes, src, 64);
       const bool pon = __shfl((int)ontrack, src, 64) != 0;
+      // (slots without a child keep values that nothing reads again: the
+      // state need not be held through the layer for them)
+      uint32_t my_orig = kHoleIdx;
       if (my_parent >= 0) {
-        const bool is_hole = my_orig == kHoleIdx;
         if (!is_hole) {
-          const float4* hp = A.hpack + (size_t)my_pos * 3;
+          const float4* hp = A.hpack + (size_t)(e0 + (int)(child.y & 0xFFFFFFu)) * 3;
           const float4 u0 = hp[0], u1 = hp[1], u2 = hp[2];
           const T hx = (T)u0.y, hy = (T)u0.z, hz = (T)u0.w;
           const T V[6] = {(T)u1.x, (T)u1.y, (T)u1.z, (T)u1.w, (T)u2.x, (T)u2.y};
+          my_orig = __float_as_uint(u2.z);
           Innov<T> in;
-          innovation<T>(Xn, Pn, hx, hy, hz, V, in);
-          apply_update<T>(Xn, Pn, in);
+          innovation<T>(X, P, hx, hy, hz, V, in);
+          apply_update<T>(X, P, in);
         }
-        if constexpr (XS) {
-#pragma unroll
-          for (int k = 0; k < 6; ++k) xs[k * 64] = Xn[k];
-#pragma unroll
-          for (int k = 0; k < NPL; ++k) xs[(6 + k) * 64] = Pn[21 - NPL + k];
-#pragma unroll
-          for (int k = 0; k < 21 - NPL; ++k) P[k] = Pn[k];
-        } else {
-#pragma unroll
-          for (int k = 0; k < 6; ++k) X[k] = Xn[k];
-#pragma unroll
-          for (int k = 0; k < 21; ++k) P[k] = Pn[k];
-        }
-        chi2 = is_hole ? pchi2 : pchi2 + my_c2;
+        chi2 = is_hole ? pchi2 : pchi2 + (T)__uint_as_float(child.x);
         nhits = is_hole ? pnh : pnh + 1;
         holes = is_hole ? pho + 1 : pho;
         if (A.dump && A.true_hits) {
@@ -729,9 +931,7 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
         hist[(l - A.first_layer) * 64 + lane] = pack_hist(my_parent, my_orig);
       }
       cnt_pred += live ? 1u : 0u;
-      cnt_scan += (unsigned)tl.scanned;
-      cnt_chi2 += (unsigned)tl.tested;
-      cnt_upd += my_parent >= 0 && my_orig != kHoleIdx ? 1u : 0u;
+      cnt_upd += my_parent >= 0 && !is_hole ? 1u : 0u;
       n_active = n_new;
     }
     if (A.counters) {
@@ -749,17 +949,10 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
       const bool act = slot < n_active;
       const uint64_t k = act ? make_key(nhits, (float)chi2, slot, 0) : kInfKey;
       const uint64_t best = group_min(k, sbase, slot, S, lane_used);
-      int bslot = -1;
-      T bc2 = 0;
-      int bn = 0;
-      if (best != kInfKey) {
-        bslot = (int)((best >> 24) & 7);
-        bc2 = shfl_t(chi2, sbase + bslot);
-        bn = __shfl(nhits, sbase + bslot, 64);
-      } else {
-        (void)shfl_t(chi2, sbase);
-        (void)__shfl(nhits, sbase, 64);
-      }
+      const int blane = sbase + (best != kInfKey ? (int)((best >> 24) & 7) : 0);
+      const int bslot = best != kInfKey ? blane - sbase : -1;
+      const T bc2 = shfl_t(chi2, blane);
+      const int bn = __shfl(nhits, blane, 64);
       const T fc2 = shfl_t(fin_chi2_reg, sbase);
       const int fvalid = lane_used ? finm[sidx * 5 + 0] : 0;
       const int fn = lane_used ? finm[sidx * 5 + 1] : 0;
@@ -767,10 +960,9 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
       if (seed_ok) {
         // state: the best lane writes its own; slot 0 writes the record
         if (!use_fin && slot == bslot) {
-          for (int k2 = 0; k2 < 6; ++k2) A.out_par[(size_t)k2 * A.ld + seed] = (float)(XS ? xs[k2 * 64] : X[k2]);
+          for (int k2 = 0; k2 < 6; ++k2) A.out_par[(size_t)k2 * A.ld + seed] = (float)X[k2];
           for (int k2 = 0; k2 < 21; ++k2)
-            A.out_cov[(size_t)k2 * A.ld + seed] =
-                (float)(XS && k2 >= 21 - NPL ? xs[(6 + k2 - 21 + NPL) * 64] : P[k2]);
+            A.out_cov[(size_t)k2 * A.ld + seed] = (float)P[k2];
           A.out_chi2[seed] = (float)chi2;
           A.out_nhits[seed] = nhits;
           A.out_status[seed] = seed_status;

@@ -47,7 +47,7 @@ __host__ __device__ inline LdsPlan lds_plan(int LB, int nwaves, int cap, int tsi
   p.stash = 0;
   p.rec = align16(p.stash + (size_t)nwaves * nst * 64 * 4);
   p.recf = align16(p.rec + (size_t)nwaves * seeds * 27 * 4);
-  const size_t tl_wave = (size_t)cap * 64 * 12;
+  const size_t tl_wave = (size_t)seeds * cap * 8 * 8;
   p.acc = align16(p.recf + (size_t)nwaves * seeds * 5 * 4);
   p.pub = align16(p.acc + (size_t)nwaves * 64 * NP * 4);
   p.tl = align16(p.pub + (size_t)nwaves * 64 * 8);

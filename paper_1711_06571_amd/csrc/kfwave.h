@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "kfhost.h"
+#include "kfreach.h"
 
 namespace {
 
@@ -390,7 +391,7 @@ __device__ inline uint32_t pack_hist(int parent, uint32_t orig24) {
 // Per-call preparation of a build in one launch: the first row_blocks blocks
 // write the fine phi index of one (event, layer, z row) each (several where
 // there are more rows than blocks), the blocks after them the packed copy of
-// kPrepThreads hits each; block 0 also resets the queue head, the per-event
+// kPackChunk hits each; block 0 also resets the queue head, the per-event
 // counters and the start tick.
 //
 // Entry j of a row's fine index is the first sorted position whose key is
@@ -405,8 +406,15 @@ __device__ inline uint32_t pack_hist(int parent, uint32_t orig24) {
 // barriers (466 us at 8.2 M hits).  Three launches (reset, index, packing)
 // before, one now: 282 -> 206 us at 8.2 M hits in 20 events, 68 -> 15
 // us for one event of 20 000 tracks, 89 -> 6 us for one of 500.
+//
+// A packing block also leaves, in the unused fourth words of its first two
+// records, bounds over its kPackChunk hits: the largest transverse and z
+// variances (infinite where a covariance is not a barrel hit's), and the
+// smallest and the largest radius, from which the hit search derives where a
+// hit of at most a given chi2 can lie (see Reach).
 constexpr int kPrepThreads = 512;
 constexpr int kPrepKeys = 4096;
+constexpr int kPackChunk = 2048;
 __global__ void __launch_bounds__(kPrepThreads)
     prep_kernel(int row_blocks, int n_rows, int n_hits, int n_phi, int n_z, int nf, const int32_t* __restrict__ offsets,
                 const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
@@ -418,13 +426,61 @@ __global__ void __launch_bounds__(kPrepThreads)
   __shared__ int32_t wsum[W];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   if ((int)blockIdx.x >= row_blocks) {
-    const int64_t p = (int64_t)((int)blockIdx.x - row_blocks) * kPrepThreads + t;
-    if (p >= n_hits) return;
+    const int64_t base = (int64_t)((int)blockIdx.x - row_blocks) * kPackChunk;
     const size_t n = (size_t)n_hits;
-    float4* o = pack + (size_t)p * 3;
-    o[0] = make_float4(phi[p], x[p], y[p], z[p]);
-    o[1] = make_float4(cov[p], cov[n + p], cov[2 * n + p], cov[3 * n + p]);
-    o[2] = make_float4(cov[4 * n + p], cov[5 * n + p], __int_as_float(orig[p]), 0.f);
+    float lam = 0.f, vzz = 0.f, rr = __builtin_inff(), rx = 0.f;
+#pragma unroll
+    for (int i = 0; i < kPackChunk / kPrepThreads; ++i) {
+      const int64_t p = base + i * kPrepThreads + t;
+      if (p >= n_hits) break;
+      const float hx = x[p], hy = y[p];
+      const float v0 = cov[p], v1 = cov[n + p], v2 = cov[2 * n + p], v3 = cov[3 * n + p], v4 = cov[4 * n + p],
+                  v5 = cov[5 * n + p];
+      float4* o = pack + (size_t)p * 3;
+      o[0] = make_float4(phi[p], hx, hy, z[p]);
+      o[1] = make_float4(v0, v1, v2, v3);
+      o[2] = make_float4(v4, v5, __int_as_float(orig[p]), 0.f);
+      // a barrel hit's covariance (z apart from x and y, both parts positive
+      // semidefinite up to rounding): the largest variance along any
+      // transverse direction, else infinity
+      const float hd = 0.5f * (v0 - v3), big = 0.5f * (v0 + v3) + __builtin_sqrtf(hd * hd + v1 * v1);
+      const bool ok = v2 == 0.f && v4 == 0.f && v0 >= 0.f && v3 >= 0.f && v5 >= 0.f &&
+                      v1 * v1 <= v0 * v3 * 1.00001f + 1e-30f && big < 1e30f && v5 < 1e30f;
+      lam = ok ? fmaxf(lam, big) : __builtin_inff();
+      vzz = ok ? fmaxf(vzz, v5) : __builtin_inff();
+      rr = fminf(rr, hx * hx + hy * hy);
+      rx = fmaxf(rx, hx * hx + hy * hy);
+    }
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+      lam = fmaxf(lam, __shfl_xor(lam, m, 64));
+      vzz = fmaxf(vzz, __shfl_xor(vzz, m, 64));
+      rr = fminf(rr, __shfl_xor(rr, m, 64));
+      rx = fmaxf(rx, __shfl_xor(rx, m, 64));
+    }
+    if (lane == 0) {
+      cnt[wave] = __float_as_int(lam);
+      cnt[W + wave] = __float_as_int(vzz);
+      cnt[2 * W + wave] = __float_as_int(rr);
+      cnt[3 * W + wave] = __float_as_int(rx);
+    }
+    __syncthreads();
+    // the chunk's bounds into the spare words of its first two records, by
+    // the threads that wrote those (a chunk of one hit has no second)
+    if (t < 2 && base + t < n_hits) {
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        lam = fmaxf(lam, __int_as_float(cnt[w]));
+        vzz = fmaxf(vzz, __int_as_float(cnt[W + w]));
+        rr = fminf(rr, __int_as_float(cnt[2 * W + w]));
+        rx = fmaxf(rx, __int_as_float(cnt[3 * W + w]));
+      }
+      if (base + 1 >= n_hits) lam = __builtin_inff();
+      float* o = (float*)(pack + (size_t)(base + t) * 3 + 2) + 3;
+      *o = __uint_as_float(t == 0 ? kfreach::bound_word(lam, vzz)
+                                  : (__float_as_uint(__builtin_sqrtf(rr) * 0.99999f) & 0xFFFF0000u) |
+                                        kfreach::bound_word(0.f, __builtin_sqrtf(rx) * 1.00001f));
+    }
     return;
   }
   if (blockIdx.x == 0) {
@@ -484,7 +540,7 @@ __global__ void __launch_bounds__(kPrepThreads)
 int launch_prep(const kf_hits* h, int refine, const int32_t* fine, const float4* pack, int32_t* queue,
                 int32_t* event_done, int64_t* start_tick, hipStream_t s) {
   const int n_rows = h->n_events * h->n_layers * h->n_z;
-  const int n_pack = (int)(((int64_t)h->n_hits + kPrepThreads - 1) / kPrepThreads);
+  const int n_pack = (int)(((int64_t)h->n_hits + kPackChunk - 1) / kPackChunk);
   const int row_blocks = n_rows < (1 << 20) ? n_rows : 1 << 20;  // (the grid stays below 2^32 threads)
   hipLaunchKernelGGL(prep_kernel, dim3(row_blocks + n_pack), dim3(kPrepThreads), 0, s, row_blocks, n_rows, h->n_hits,
                      h->n_phi, h->n_z, h->n_phi * refine, h->offsets, h->x, h->y, h->z, h->phi, h->cov, h->orig,
