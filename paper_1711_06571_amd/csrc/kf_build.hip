@@ -201,10 +201,10 @@ __device__ inline void pool_cut(const BuildArgs& A, const Pool& po, const Group&
 // A candidate is wide when its window may hold more than kWidePairs pairs;
 // it then first searches where its kProbeHits best hits should lie.
 #ifndef KF_WIDE_PAIRS
-#define KF_WIDE_PAIRS 128
+#define KF_WIDE_PAIRS 192
 #endif
 #ifndef KF_PROBE_HITS
-#define KF_PROBE_HITS 20
+#define KF_PROBE_HITS 16
 #endif
 constexpr float kWidePairs = KF_WIDE_PAIRS, kProbeHits = KF_PROBE_HITS;
 
@@ -289,29 +289,45 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
   const int32_t* frow = A.fine + ((size_t)ev * A.n_layers + l) * nz * (nf + 1);
   // ranges: (row, interval) for every row, 1 << sh intervals per row (two
   // where the window wraps at 2 pi, four of a Reach)
-  Reach rq = {0.f, 0u, 0u};
+  Reach rq = {0.f, 0.f, 0u, 0u};
+  float al[2] = {1.f, 1.f}, ah[2] = {0.f, 0.f};  // the row's arcs
   int sh = phi_parts(phip, hw);
   int R = pok ? rw.n() << sh : 0;
   const float chi2_cut = A.chi2_cut;
   float thr = __builtin_inff();  // chi2 of a hit that may enter the pool
   bool lim = false;              // any pool was cut: thr counts
-  // range r of this candidate: its stored-value interval and its sorted
-  // positions from the fine index (read one range ahead)
-  auto range_of = [&](int r, float& a, float& b, int& q0, int& q1) {
+  // Ranges of iteration r: one range, or, where a row is one interval, two
+  // rows (most windows that cross a row edge are then done in one
+  // iteration): the stored-value interval and the sorted positions from the
+  // fine index (read one iteration ahead).
+  auto iters = [&]() { return sh == 0 ? (R + 1) >> 1 : R; };
+  auto range_of = [&](int it, float& a, float& b, int& q0, int& q1, int& q2, int& q3) {
     a = 1.f;
     b = 0.f;
     q0 = 0;
     q1 = 0;
+    q2 = 0;
+    q3 = 0;
+    const int r = sh == 0 ? 2 * it : it;
     if (r < R) {
       const int row = rw.at(r >> sh), i = r & ((1 << sh) - 1);
-      if (sh == 2)
-        reach_part(rq, suu, suw, sww, k_sqrt(fx * fx + fy * fy), fz, phip, hw, fdz + kEpsZ, row, nz, A.z_half, i, a, b);
-      else
+      if (sh == 2) {
+        if (i == 0)
+          reach_arcs(rq, suu, suw, sww, k_sqrt(fx * fx + fy * fy), fz, hw, fdz + kEpsZ, row, nz, A.z_half, al, ah);
+        arc_part(phip, i & 2 ? al[1] : al[0], i & 2 ? ah[1] : ah[0], i & 1, a, b);
+      } else {
         phi_part(phip, hw, i, a, b);
+      }
       if (a <= b) {
         const int32_t* f = frow + (size_t)row * (nf + 1);
-        q0 = f[fine_key(a, inv, nf)];
-        q1 = f[fine_key(b, inv, nf) + 1];
+        const int ka = fine_key(a, inv, nf), kb = fine_key(b, inv, nf) + 1;
+        q0 = f[ka];
+        q1 = f[kb];
+        if (sh == 0 && r + 1 < R) {
+          const int32_t* f2 = frow + (size_t)rw.at(r + 1) * (nf + 1);
+          q2 = f2[ka];
+          q3 = f2[kb];
+        }
       }
     }
   };
@@ -320,18 +336,18 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
   if (gr.used && gr.slot == 0) po.cnt[gr.sidx] = 0;
 
   float an = 1.f, bn = 0.f;
-  int p0n = 0, p1n = 0;
+  int p0n = 0, p1n = 0, p2n = 0, p3n = 0;
   bool wide = false, pruned = false;
-  float c2b = chi2_cut, del = 0.f;
+  float c2b = chi2_cut;
   bool look = A.counters == nullptr;  // wide windows still to be looked for
   bool again = false;                 // a wide candidate's bound still to be checked
-  int Rmax = wave_max(R);
+  int Rmax = wave_max(iters());
   // (one call of range_of in the code: the pass over the ranges starts one
   // before the first, where only the first is read)
   for (int r = -1;;) {
     const float a = an, b = bn;
-    const int p0 = p0n, p1 = p1n;
-    range_of(r + 1, an, bn, p0n, p1n);
+    const int p0 = p0n, p1 = p1n, p2 = p2n, p3 = p3n;
+    range_of(r + 1, an, bn, p0n, p1n, p2n, p3n);
     if (r < 0 && look) {
       look = false;
       const int c0 = p1n - p0n;  // the middle row
@@ -340,27 +356,32 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
         if (wide) {
           const int32_t* of = A.offsets + ((size_t)ev * A.n_layers + l) * ((size_t)A.n_phi * nz + 1);
           reach_bounds(A.hpack, A.n_hits, of[rw.lo * A.n_phi], of[(rw.hi + 1) * A.n_phi], rq);
-          del = reach_del(rq, suu, suw, sww);
-          wide = del > 0.f;
+          wide = rq.usable(suu, sww);
           if (wide) {
             const float area = 4.f * fminf(hw, 3.1415927f) * k_sqrt(fx * fx + fy * fy) * A.z_half / (float)nz;
-            const float s2 = (suu + rq.lam()) * (sww + rq.vzz()) - suw * suw;
-            c2b = fminf(kProbeHits * area / (3.1415927f * k_sqrt(s2) * (float)c0), chi2_cut);
-            rq.c2 = c2b * reach_margin(del);
+            const float s00 = fabsf(suu) + rq.lam(), s11 = sww + rq.vzz();
+            const float s2 = fmaxf(s00 * s11 - suw * suw, 1e-6f * s00 * s11);
+            const bool none = rq.none(suu, suw, sww);
+            if (!none) c2b = fminf(kProbeHits * area / (3.1415927f * k_sqrt(s2) * (float)c0), chi2_cut);
+            rq.set(c2b, suu, suw, sww);
             rw = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
+            if (none) rw.hi = rw.lo - 1;
             sh = 2;
             R = rw.n() << sh;
           }
         }
         again = __any(wide && c2b < chi2_cut);
-        Rmax = wave_max(R);
+        Rmax = wave_max(iters());
         continue;
       }
     }
     const int cnt = r >= 0 && p1 > p0 ? p1 - p0 : 0;
+    const int all = cnt + (r >= 0 && p3 > p2 ? p3 - p2 : 0);
     int total = 0;
-    const int off = wave_excl_scan(cnt, lane, total);
-    const int pb = p0 - off;  // sorted position of pair k of this candidate: pb + k
+    const int off = wave_excl_scan(all, lane, total);
+    // sorted position of pair k of this candidate: pb + k, from pair `turn` on
+    // (the second row) pb2 + k
+    const int pb = p0 - off, turn = off + cnt, pb2 = p2 - turn;
     int carry = 0;  // candidate of the previous round's last pair
     // each lane takes NP pairs per round (pair base + 64 h + lane): their
     // loads share one round trip
@@ -370,7 +391,7 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
       // its slot in its half, else the one whose pairs run on from before
 #pragma unroll
       for (int h = 0; h < NPT; ++h) start[h * 64 + lane] = -1;
-      if (cnt > 0 && off >= base && off - base < 64 * NPT) start[off - base] = lane;
+      if (all > 0 && off >= base && off - base < 64 * NPT) start[off - base] = lane;
       lds_order();
       int c[NPT], p[NPT];
       bool valid[NPT];
@@ -386,7 +407,8 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
         carry = __builtin_amdgcn_readlane(c[h], 63);
         const int k = base + 64 * h + lane;
         valid[h] = k < total;
-        p[h] = __shfl(pb, c[h], 64) + k;
+        const int c1 = __shfl(pb, c[h], 64), c2 = __shfl(pb2, c[h], 64);
+        p[h] = (k < __shfl(turn, c[h], 64) ? c1 : c2) + k;
         ca[h] = __shfl(a, c[h], 64);
         cb[h] = __shfl(b, c[h], 64);
         cx[h] = __shfl(fx, c[h], 64);
@@ -454,33 +476,48 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
           }
         }
       }
-      // the accepted hits of each half into their seeds' pools
+      // the accepted hits into their seeds' pools
+      bool pend[NPT], any = false;
 #pragma unroll
       for (int h = 0; h < NPT; ++h) {
-        if (!__any(acc[h])) continue;
+        pend[h] = acc[h];
+        any = any || acc[h];
+      }
+      if (!__any(any)) continue;
+      int sd[NPT];
+      uint32_t ref[NPT];
+#pragma unroll
+      for (int h = 0; h < NPT; ++h) {
         if (acc[h]) po.seen[c[h]] = 1;
-        const int sd = c[h] * inv_s >> 16;
-        const uint32_t ref = ((uint32_t)(c[h] - sd * gr.S) << 24) | (uint32_t)(p[h] - __shfl(e0, c[h], 64));
-        bool pend = acc[h];
-        if (lim) {  // (the shuffle by all lanes)
-          const float ct = __shfl(thr, c[h], 64);
-          pend = pend && c2[h] <= ct;
-        }
-        for (;;) {
-          if (pend) {
-            const int i = atomicAdd(&po.cnt[sd], 1);
-            if (i < po.full) {
-              po.e[sd * po.stride + i] = make_uint2(__float_as_uint(c2[h]), ref);
-              pend = false;
-            }
+        sd[h] = c[h] * inv_s >> 16;
+        ref[h] = ((uint32_t)(c[h] - sd[h] * gr.S) << 24) | (uint32_t)(p[h] - __shfl(e0, c[h], 64));
+      }
+      for (;;) {
+        if (lim) {
+#pragma unroll
+          for (int h = 0; h < NPT; ++h) {
+            const float ct = __shfl(thr, c[h], 64);  // (by all lanes)
+            pend[h] = pend[h] && c2[h] <= ct;
           }
-          const unsigned long long pm = __ballot(pend);
-          if (!pm) break;
-          pool_cut<T>(A, po, gr, __builtin_amdgcn_readlane(sd, (int)__builtin_ctzll(pm)), lane, chi2, nhits, e0, thr, cut);
-          lim = true;
-          const float ct = __shfl(thr, c[h], 64);
-          pend = pend && c2[h] <= ct;
         }
+        int at[NPT];
+#pragma unroll
+        for (int h = 0; h < NPT; ++h) at[h] = pend[h] ? atomicAdd(&po.cnt[sd[h]], 1) : po.full;
+        unsigned long long pm = 0ull;
+        int over = 0;  // a seed whose pool is full
+#pragma unroll
+        for (int h = 0; h < NPT; ++h) {
+          if (at[h] < po.full) {
+            po.e[sd[h] * po.stride + at[h]] = make_uint2(__float_as_uint(c2[h]), ref[h]);
+            pend[h] = false;
+          }
+          const unsigned long long q = __ballot(pend[h]);
+          if (q) over = __builtin_amdgcn_readlane(sd[h], (int)__builtin_ctzll(q));
+          pm |= q;
+        }
+        if (!pm) break;
+        pool_cut<T>(A, po, gr, over, lane, chi2, nhits, e0, thr, cut);
+        lim = true;
       }
     }
     if (++r < Rmax) continue;
@@ -504,18 +541,19 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
       }
       if (__any(miss)) redo |= sm;
     }
+    const int R0 = rw.n();
     R = 0;
     if (!redo) break;
     if (redo >> lane & 1ull) {
       if (gr.slot == 0) po.cnt[gr.sidx] = 0;
       if (!pruned) po.seen[lane] = 0;
-      if (wide) {
-        rq.c2 = c2b * reach_margin(del);
+      if (wide && R0 > 0) {
+        rq.set(c2b, suu, suw, sww);
         rw = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
       }
       R = pok ? rw.n() << sh : 0;
     }
-    Rmax = wave_max(R);
+    Rmax = wave_max(iters());
     r = -1;
   }
   __builtin_amdgcn_s_waitcnt(0);
@@ -542,14 +580,54 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
 // wave).
 //
 // Returns the number of children kept; n_all: children before the cut.
-template <int NI>
-__device__ inline void rank_items(const uint64_t* kv, const uint64_t* key, int* rank, int m, int mmax) {
-  for (int i = 0; i < mmax; ++i) {
-    uint64_t k = kv[i];
-    k = i < m ? k : kInfKey;
+template <typename T, int NI>
+__device__ inline void rank_items(const Pool& po, const Group& gr, const uint2* pe, uint64_t* kv, uint64_t* wv, int m,
+                                  int mmax, int cap, T chi2, int nhits) {
+  uint2 e[NI];
+  T pc[NI];
+  int pn[NI], rank[NI];
+  uint64_t key[NI];
+  // (each stage for all of the lane's children, so that its LDS operations
+  // are in flight together)
 #pragma unroll
-    for (int t = 0; t < NI; ++t) rank[t] += k < key[t] ? 1 : 0;
+  for (int t = 0; t < NI; ++t) {
+    const int j = gr.slot + t * gr.S;
+    e[t] = pe[gr.used && j < m ? j : 0];
   }
+#pragma unroll
+  for (int t = 0; t < NI; ++t) {
+    const int src = gr.base + (gr.used && gr.slot + t * gr.S < m ? (int)(e[t].y >> 24) : gr.slot);
+    pc[t] = shfl_t(chi2, src);
+    pn[t] = __shfl(nhits, src, 64);
+  }
+#pragma unroll
+  for (int t = 0; t < NI; ++t) {
+    const int j = gr.slot + t * gr.S;
+    const bool hit = (e[t].y & 0xFFFFFFu) != kNoHit;
+    const float c2 = __uint_as_float(e[t].x);
+    key[t] = ((uint64_t)(31 - pn[t] - (hit ? 1 : 0)) << 59) | ((uint64_t)chi2_bits((float)(pc[t] + (T)c2)) << 28) |
+             ((uint64_t)(e[t].y >> 24) << 25) | ((uint64_t)(chi2_bits(c2) >> 12) << 6) | (uint64_t)j;
+    if (!gr.used || j >= m) key[t] = kInfKey;
+    if (gr.used && j < po.stride) kv[j] = key[t];
+    rank[t] = 0;
+  }
+  lds_order();
+  // (the keys past m are infinite up to NI S >= mmax, and the rest of the
+  // stride is not read: both are multiples of 4 apart from the last round)
+  for (int i = 0; i < mmax; i += 4) {
+    uint64_t k[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) k[u] = kv[i + u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (i + u >= NI * gr.S) k[u] = kInfKey;
+#pragma unroll
+      for (int t = 0; t < NI; ++t) rank[t] += k[u] < key[t] ? 1 : 0;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NI; ++t)
+    if (key[t] != kInfKey && rank[t] <= cap) wv[rank[t]] = key[t];
 }
 template <typename T>
 __device__ inline int best_children(const BuildArgs& A, const Pool& po, const Group& gr, uint64_t* keys, uint64_t* win,
@@ -568,35 +646,9 @@ __device__ inline int best_children(const BuildArgs& A, const Pool& po, const Gr
       pe[m0 + __builtin_popcountll(hm & ((1ull << lane) - 1ull))] = make_uint2(0u, ((uint32_t)gr.slot << 24) | kNoHit);
     lds_order();
     const int mmax = wave_max(m);
-    uint64_t key[NT];
-    int rank[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      key[t] = kInfKey;
-      rank[t] = 0;
-      if (t * S < mmax) {
-        const int j = gr.slot + t * S;
-        const bool in = gr.used && j < m;
-        const uint2 e = pe[in ? j : 0];
-        const int src = gr.base + (in ? (int)(e.y >> 24) : gr.slot);
-        const T pc = shfl_t(chi2, src);
-        const int pn = __shfl(nhits, src, 64);
-        const bool hit = (e.y & 0xFFFFFFu) != kNoHit;
-        const float c2 = __uint_as_float(e.x);
-        if (in) {
-          key[t] = ((uint64_t)(31 - pn - (hit ? 1 : 0)) << 59) | ((uint64_t)chi2_bits((float)(pc + (T)c2)) << 28) |
-                   ((uint64_t)(e.y >> 24) << 25) | ((uint64_t)(chi2_bits(c2) >> 12) << 6) | (uint64_t)j;
-          kv[j] = key[t];
-        }
-      }
-    }
-    lds_order();
-    if (mmax <= 2 * S) rank_items<2>(kv, key, rank, m, mmax);
-    else if (mmax <= 4 * S) rank_items<4>(kv, key, rank, m, mmax);
-    else rank_items<NT>(kv, key, rank, m, mmax);
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-      if (t * S < mmax && key[t] != kInfKey && rank[t] <= cap) wv[rank[t]] = key[t];
+    if (mmax <= 2 * S) rank_items<T, 2>(po, gr, pe, kv, wv, m, mmax, cap, chi2, nhits);
+    else if (mmax <= 4 * S) rank_items<T, 4>(po, gr, pe, kv, wv, m, mmax, cap, chi2, nhits);
+    else rank_items<T, NT>(po, gr, pe, kv, wv, m, mmax, cap, chi2, nhits);
     lds_order();
     const bool kept = gr.used && gr.slot < m;  // (slot < cap)
     const uint64_t k0 = wv[kept ? gr.slot : 0];
@@ -638,8 +690,14 @@ __device__ inline int best_children(const BuildArgs& A, const Pool& po, const Gr
 #ifndef KF_LEARNED_F64_NPT
 #define KF_LEARNED_F64_NPT 2
 #endif
+#ifndef KF_F64_NPT
+#define KF_F64_NPT NP
+#endif
+#ifndef KF_F32_NPT
+#define KF_F32_NPT NP
+#endif
 template <typename T, bool LEARNED>
-constexpr int NPT_OF = (sizeof(T) == 8 && LEARNED) ? KF_LEARNED_F64_NPT : NP;
+constexpr int NPT_OF = (sizeof(T) == 8 && LEARNED) ? KF_LEARNED_F64_NPT : sizeof(T) == 8 ? KF_F64_NPT : KF_F32_NPT;
 
 template <typename T, bool LEARNED, bool HYB>
 __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
@@ -864,9 +922,14 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
       coop_scan<T, NPT_OF<T, LEARNED>>(A, kv64<T>(ev), e0, l, pok, Xp, Pp, dphi_w, dz_w, chi2, nhits, hole_ok, gr, po,
                                        start, lane, seen, cut, cnt_scan, cnt_chi2);
       const int nchild = (seen ? 1 : 0) + (hole_ok ? 1 : 0);
-      // finished candidates of this layer (live, no child) compete for the record
-      if (__any(live && nchild == 0)) {  // (most layers have none)
-        const bool stopped = live && nchild == 0;
+      // Finished candidates of this layer (live, no child) compete for the
+      // record.  Slot 0 has the seed's most hits; where a candidate with as
+      // many found a hit, the seed ends with more than any that stops here
+      // has, which then need not compete.
+      const int top_hits = __shfl(nhits, sbase, 64);
+      const unsigned long long ahead = __ballot(live && seen && nhits == top_hits) & (((1ull << S) - 1ull) << sbase);
+      const bool stopped = live && nchild == 0 && ahead == 0ull;
+      if (__any(stopped)) {
         uint64_t fk = stopped ? make_key(nhits, (float)chi2, slot, 0) : kInfKey;
         const uint64_t best = group_min(fk, sbase, slot, S, lane_used);
         const int ws = (int)((best >> 24) & 7);

@@ -61,92 +61,119 @@ KFR uint32_t bound_word(float a, float b) {
 }
 
 // Where a layer's hits of chi2 at most c2 can lie: with S = [s00 s01; s01
-// s11] and residuals r0 (along the arc) and r1 (z),
-//   chi2 = r1^2 / s11 + (r0 - s01/s11 r1)^2 / (s00 - s01^2/s11),
+// s11] and residuals r0 (along the arc) and r1 (z), D = det S and k = s01/s11,
+//   D chi2 = num = s11 (r0 - k r1)^2 + D/s11 r1^2,
 // so per z row r0 lies in a strip, and r0 = radius * sin(angle from the
 // prediction): up to two arcs of stored phi, the second mirrored about the
 // quarter turn.  s01 is the prediction's; s00 and s11 are the prediction's
 // (suu, sww) plus at most the largest variances of the hits looked at, whose
 // covariances couple z neither to x nor to y.
+//
+// The builder computes num and D in FP32: num loses at most 10 ulp of
+// s11 r0^2 + s00 r1^2 and D gains at most 4 ulp of s00 s11, so a hit whose
+// computed chi2 is at most c2 has
+//   (r0 - k r1)^2 <= c2 (C + 4u s00) - C r1^2 / s11 + 10u (r0^2 + s00/s11 r1^2)
+// with C = D / s11, which near full correlation may be negative (u = 2^-24;
+// twice the factors are used).  The same bounds r1 where 1 - rho^2 is not
+// lost in rounding: c2_z is c2 with that margin, else infinite.
 struct Reach {
-  float c2;      // (with the margin below)
+  float c2, c2_z;
   uint32_t v;    // largest transverse and z variances of the hits (bound_word)
   uint32_t rad;  // smallest and largest radius, upper halves
   KFR float lam() const { return bits_f(v & 0xFFFF0000u); }
   KFR float vzz() const { return bits_f(v << 16); }
-  KFR float dz(float sww) const { return sqrtf(c2 * (sww + vzz())) * 1.0001f + kEpsZ; }
+  KFR float rlo() const { return bits_f(rad & 0xFFFF0000u); }
+  KFR float rhi() const { return bits_f(rad << 16); }
+  KFR float dz(float sww) const { return sqrtf(c2_z * (sww + vzz())) * 1.0001f + kEpsZ; }
+  // whether a bound can be given at all
+  KFR bool usable(float suu, float sww) const {
+    return lam() < 1e30f && vzz() < 1e30f && (rad >> 16) != 0u && fabsf(suu) < 1e30f && sww > 0.f && sww < 1e30f;
+  }
+  // whether no hit can have a positive determinant (an FP32 covariance that
+  // lost its positivity): the builder then accepts none
+  KFR bool none(float suu, float suw, float sww) const {
+    const float s00 = fabsf(suu) + lam();
+    return suu + lam() - suw * suw / (sww + vzz()) < -3e-6f * s00;
+  }
+  // sets the bound (>= 0); rho^2 is largest without the hit's own variances
+  KFR void set(float bound, float suu, float suw, float sww) {
+    const float e = suu - 1e-5f * lam(), d = 1.f - suw * suw / (e * sww) - 2e-7f;
+    c2 = bound;
+    c2_z = e > 0.f && d > 1e-5f ? bound * (1.f + 4e-6f / d) * 1.0001f : 1e30f;
+  }
 };
-// 1 - rho^2 of S at least (without the hit's own variances), or 0 where no
-// bound can be given.
-KFR float reach_del(const Reach& q, float suu, float suw, float sww) {
-  const float e = suu - 1e-5f * q.lam();
-  const float d = 1.f - suw * suw / (e * sww) - 2e-7f;
-  return e > 0.f && sww > 0.f && d > 1e-5f && q.lam() < 1e30f && q.vzz() < 1e30f && (q.rad >> 16) != 0u ? d : 0.f;
-}
-// The chi2 computed in FP32 may fall below its exact value by a part of
-// 1.5e-6 / (1 - rho^2): the numerator's terms lose 10 ulp of their sum, of
-// which at least 1 - |rho| remains, the determinant 4 ulp of s00 s11.
-KFR float reach_margin(float del) { return (1.f + 4e-6f / del) * 1.0001f; }
 
-// Part i (0..3) of row `row`: arc i / 2, cut where it wraps; a > b: empty.
-// The parts are disjoint.  phip, z: the prediction; rc its radius; hw, dzw:
-// the window's half-widths.
-KFR void reach_part(const Reach& q, float suu, float suw, float sww, float rc, float z, float phip, float hw, float dzw,
-                    int row, int nz, float zh, int i, float& a, float& b) {
+// The arcs of row `row` as angles from the prediction, clipped to the window:
+// [lo[0], hi[0]] and [lo[1], hi[1]], empty where lo > hi; an arc of [-4, 4] is
+// the whole circle.  rc, z: the prediction's radius and z; hw, dzw: the
+// window's half-widths.
+KFR void reach_arcs(const Reach& q, float suu, float suw, float sww, float rc, float z, float hw, float dzw, int row, int nz,
+                    float zh, float lo[2], float hi[2]) {
   const float pi = 3.1415927f, eps = 4e-5f;
-  const float lam = q.lam(), s11 = sww + q.vzz();
+  const float lam = q.lam(), s00 = fabsf(suu) + lam, s11 = sww + q.vzz();
   const float rh = 2.f * zh / (float)nz, zb = q.dz(sww), zm = zb < dzw ? zb : dzw;
-  a = 1.f;
-  b = 0.f;
+  lo[0] = lo[1] = 1.f;
+  hi[0] = hi[1] = 0.f;
   // residuals in z of the row's hits (the end rows hold all hits beyond)
   float l1 = row == 0 ? -zm : (float)row * rh - zh - z - kEpsZ;
   float h1 = row == nz - 1 ? zm : (float)(row + 1) * rh - zh - z + kEpsZ;
   l1 = l1 < -zm ? -zm : l1;
   h1 = h1 > zm ? zm : h1;
-  const float m1 = l1 > 0.f ? l1 : (h1 < 0.f ? -h1 : 0.f);
-  const float rem = q.c2 - m1 * m1 / s11 * 0.9999f;
-  if (!(l1 <= h1) || !(rem >= 0.f)) return;
-  const float cond = suu + lam - suw * suw / s11 + 2e-6f * (suu + lam);
+  if (!(zm < 1e9f)) {  // (nothing to gain, and the squares below stay finite)
+    lo[0] = hw < 3.14159f ? -hw : -4.f;
+    hi[0] = hw < 3.14159f ? hw : 4.f;
+    return;
+  }
+  if (!(l1 <= h1)) return;
+  const float m1 = l1 > 0.f ? l1 : (h1 < 0.f ? -h1 : 0.f), M1 = fmaxf(fabsf(l1), fabsf(h1));
+  const float rhi = q.rhi(), rlo = q.rlo();
+  const float cmax = suu + lam - suw * suw / s11 + 2e-6f * s00, cmin = suu - 1e-5f * lam - suw * suw / sww - 2e-6f * s00;
+  const float w2 = q.c2 * (fmaxf(cmax, 0.f) + 5e-7f * s00) * 1.0002f -
+                   (cmin > 0.f ? cmin * m1 * m1 / s11 : cmin * M1 * M1 / sww) +
+                   1.2e-6f * (rhi * rhi + s00 / sww * M1 * M1);
+  if (!(w2 >= 0.f)) return;
   const float ka = suw / sww, kb = suw / s11;
   const float x0 = ka * l1, x1 = ka * h1, x2 = kb * l1, x3 = kb * h1;
-  const float h = sqrtf(rem * cond) * 1.0001f + 4e-6f * rc + 1e-5f * (fabsf(x0) + fabsf(x1));
+  const float h = sqrtf(w2) * 1.0001f + 4e-6f * rc + 1e-5f * (fabsf(x0) + fabsf(x1));
   const float r0l = fminf(fminf(x0, x1), fminf(x2, x3)) - h, r0h = fmaxf(fmaxf(x0, x1), fmaxf(x2, x3)) + h;
-  const float rlo = bits_f(q.rad & 0xFFFF0000u), rhi = bits_f(q.rad << 16);
   const float sl = r0l / (r0l < 0.f ? rlo : rhi), su = r0h / (r0h > 0.f ? rlo : rhi);
   if (!(sl < 1.f) || !(su > -1.f)) return;
   const bool ol = sl < -0.9999f, ou = su > 0.9999f;
   const float dl = ol ? -0.5f * pi : asinf(sl) - eps, dh = ou ? 0.5f * pi : asinf(su) + eps;
-  float u0, u1;  // the arc, as angles from the prediction
   if (ol && ou) {  // every angle
-    if (i & 2) return;
-    if (hw >= 3.14159f) {
-      a = i == 0 ? 0.f : 1.f;
-      b = i == 0 ? kTwoPiF : 0.f;
-      return;
-    }
-    u0 = -hw;
-    u1 = hw;
+    lo[0] = hw < 3.14159f ? -hw : -4.f;
+    hi[0] = hw < 3.14159f ? hw : 4.f;
   } else if (ol || ou) {  // the two arcs meet at a quarter turn
-    if (i & 2) return;
-    u0 = ou ? dl : -pi - dh;
-    u1 = ou ? pi - dl : dh;
+    lo[0] = ou ? dl : -pi - dh;
+    hi[0] = ou ? pi - dl : dh;
     if (hw < 0.5f * pi) {
-      u0 = fmaxf(u0, -hw);
-      u1 = fminf(u1, hw);
+      lo[0] = fmaxf(lo[0], -hw);
+      hi[0] = fminf(hi[0], hw);
     }
-  } else if (i & 2) {
-    if (!(pi - dh <= hw + eps) && !(pi + dl <= hw + eps)) return;  // the window does not reach it
-    u0 = pi - dh;
-    u1 = pi - dl;
   } else {
-    u0 = fmaxf(dl, -hw);
-    u1 = fminf(dh, hw);
+    lo[0] = fmaxf(dl, -hw);
+    hi[0] = fminf(dh, hw);
+    if (pi - dh <= hw + eps || pi + dl <= hw + eps) {  // the window reaches the second
+      lo[1] = pi - dh;
+      hi[1] = pi - dl;
+    }
   }
-  if (!(u0 <= u1)) return;
-  float lo = phip + u0, hi = phip + u1;
-  if (lo >= kTwoPiF) { lo -= kTwoPiF; hi -= kTwoPiF; }
-  if (hi < 0.f) { lo += kTwoPiF; hi += kTwoPiF; }
-  wrap_part(lo, hi, i, a, b);
+}
+// Part i (0, 1) of an arc in stored phi, cut where it wraps; a > b: empty.
+// The parts of a row's arcs are disjoint.
+KFR void arc_part(float phip, float lo, float hi, int i, float& a, float& b) {
+  a = 1.f;
+  b = 0.f;
+  if (!(lo <= hi)) return;
+  if (hi - lo > 7.f) {
+    a = i == 0 ? 0.f : 1.f;
+    b = i == 0 ? kTwoPiF : 0.f;
+    return;
+  }
+  float u0 = phip + lo, u1 = phip + hi;
+  if (u0 >= kTwoPiF) { u0 -= kTwoPiF; u1 -= kTwoPiF; }
+  if (u1 < 0.f) { u0 += kTwoPiF; u1 += kTwoPiF; }
+  wrap_part(u0, u1, i, a, b);
 }
 
 }  // namespace kfreach
