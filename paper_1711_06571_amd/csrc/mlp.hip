@@ -39,9 +39,13 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-// One block = one wave = 64 rows.  Writes the block's partial gradient of
-// the summed loss (not yet divided by 2N) and the summed loss.
-__global__ void __launch_bounds__(64) grad_kernel(const float* __restrict__ blk, const float* __restrict__ rows,
+// One block = four waves = 64 rows; a wave takes 16 of a layer's 64 columns
+// (of the weight gradients, 16 rows).  Writes the block's partial gradient of
+// the summed loss (not yet divided by 2N) and the summed loss.  The chain of
+// the five products and the transcendentals between them bounds it, so the
+// columns are spread: 4 096 rows in 30 us with one wave per block, in 11
+// with four.  Every sum keeps its order.
+__global__ void __launch_bounds__(256) grad_kernel(const float* __restrict__ blk, const float* __restrict__ rows,
                                                   int n, float* __restrict__ partial) {
   __shared__ __align__(16) uint16_t XT[32 * P];    // inputs, [k][row]
   __shared__ __align__(16) uint16_t XR[64 * P];    // inputs, [row][k]; later dZ1 [unit][row]
@@ -50,9 +54,10 @@ __global__ void __launch_bounds__(64) grad_kernel(const float* __restrict__ blk,
   __shared__ __align__(16) uint16_t H2R[64 * P];   // [row][unit]
   __shared__ __align__(16) uint16_t DZR[64 * P];   // dZ2 [row][unit]
   __shared__ __align__(16) uint16_t DZT[64 * P];   // dZ2 [unit][row]
-  __shared__ float G[64 * 2];                      // dL/do per row
-  const int lane = threadIdx.x;
+  __shared__ float G[64 * 2];                      // head outputs, then dL/do, per row
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, kq = lane >> 4;
+  const int nt = wv, col = nt * 16 + r16;
   const int row = blockIdx.x * 64 + lane;
   const bool valid = row < n;
   const uint16_t* W = (const uint16_t*)(blk + KFMLP_HEADER_FLOATS);
@@ -63,87 +68,86 @@ __global__ void __launch_bounds__(64) grad_kernel(const float* __restrict__ blk,
   {
     const float* src = rows + (size_t)(valid ? row : 0) * KFMLP_DUMP_ROW;
 #pragma unroll
-    for (int k = 0; k < 27; ++k) {
+    for (int k0 = 0; k0 < 28; k0 += 4) {
+      const int k = k0 + wv;
+      if (k >= 27) continue;
       const float v = valid ? (src[k] - blk[KFMLP_OFF_MU + k]) * blk[KFMLP_OFF_ISD + k] : 0.f;
       const uint16_t b = f_to_bf16(v);
       XR[lane * P + k] = b;
       XT[k * P + lane] = b;
     }
-#pragma unroll
-    for (int k = 27; k < 32; ++k) { XR[lane * P + k] = 0; XT[k * P + lane] = 0; }
+    for (int k = 27 + wv; k < 32; k += 4) { XR[lane * P + k] = 0; XT[k * P + lane] = 0; }
     d[0] = valid ? src[27] : 0.f;
     d[1] = valid ? src[28] : 0.f;
   }
   __syncthreads();
   // forward, keeping the pre-activations in registers (tile layout)
-  f32x4 z1[4][4], z2[4][4];
+  f32x4 z1[4], z2[4];
+  {
+    const bf16x8 w1 = load8(W + KFMLP_W1 + col * 32 + 8 * kq);
+    const float b1 = blk[KFMLP_OFF_B1 + col];
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    const bf16x8 a = load8(XR + (mt * 16 + r16) * P + 8 * kq);
+    for (int mt = 0; mt < 4; ++mt) {
+      z1[mt] = mfma(load8(XR + (mt * 16 + r16) * P + 8 * kq), w1, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      z1[mt][nt] = mfma(a, load8(W + KFMLP_W1 + (nt * 16 + r16) * 32 + 8 * kq), f32x4{0.f, 0.f, 0.f, 0.f});
-      const float b1 = blk[KFMLP_OFF_B1 + nt * 16 + r16];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) z1[mt][nt][i] += b1;
+      for (int i = 0; i < 4; ++i) z1[mt][i] += b1;
       f32x4 h;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) h[i] = gelu(z1[mt][nt][i]);
-      store_bf16_tile_rows(H1R, mt * 16, nt * 16 + r16, h);
-      store_bf16_tile_cols(H1T, mt * 16, nt * 16 + r16, h);
+      for (int i = 0; i < 4; ++i) h[i] = gelu(z1[mt][i]);
+      store_bf16_tile_rows(H1R, mt * 16, col, h);
+      store_bf16_tile_cols(H1T, mt * 16, col, h);
     }
   }
   __syncthreads();
+  {
+    const uint16_t* wr = W + KFMLP_W2 + col * 64;
+    const bf16x8 w20 = load8(wr + 8 * kq), w21 = load8(wr + 32 + 8 * kq);
+    const float b2 = blk[KFMLP_OFF_B2 + col];
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    const bf16x8 a0 = load8(H1R + (mt * 16 + r16) * P + 8 * kq);
-    const bf16x8 a1 = load8(H1R + (mt * 16 + r16) * P + 32 + 8 * kq);
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const uint16_t* wr = W + KFMLP_W2 + (nt * 16 + r16) * 64;
-      f32x4 acc = mfma(a0, load8(wr + 8 * kq), f32x4{0.f, 0.f, 0.f, 0.f});
-      acc = mfma(a1, load8(wr + 32 + 8 * kq), acc);
-      const float b2 = blk[KFMLP_OFF_B2 + nt * 16 + r16];
+    for (int mt = 0; mt < 4; ++mt) {
+      f32x4 acc = mfma(load8(H1R + (mt * 16 + r16) * P + 8 * kq), w20, f32x4{0.f, 0.f, 0.f, 0.f});
+      acc = mfma(load8(H1R + (mt * 16 + r16) * P + 32 + 8 * kq), w21, acc);
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[i] += b2;
-      z2[mt][nt] = acc;
+      z2[mt] = acc;
       f32x4 h;
 #pragma unroll
       for (int i = 0; i < 4; ++i) h[i] = gelu(acc[i]);
-      store_bf16_tile_rows(H2R, mt * 16, nt * 16 + r16, h);
+      store_bf16_tile_rows(H2R, mt * 16, col, h);
     }
   }
   __syncthreads();
-  // head, in FP32 from the BF16 activations of this lane's row
-  float o[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  // head, in FP32 from the BF16 activations of this lane's row: output wv
+  if (wv < 2) {
     float s = 0.f;
-    for (int k = 0; k < 64; ++k) s += bf16_to_f(W[KFMLP_W3 + j * 64 + k]) * bf16_to_f(H2R[lane * P + k]);
-    o[j] = s + blk[KFMLP_OFF_B3 + j];
+#pragma unroll 16
+    for (int k = 0; k < 64; ++k) s += bf16_to_f(W[KFMLP_W3 + wv * 64 + k]) * bf16_to_f(H2R[lane * P + k]);
+    G[lane * 2 + wv] = s + blk[KFMLP_OFF_B3 + wv];
   }
+  __syncthreads();
+  const float o[2] = {G[lane * 2], G[lane * 2 + 1]};
+  __syncthreads();
   float loss = 0.f;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const float w = blk[KFMLP_OFF_SCALE + j] * softplus(o[j]);
     const float gw = w > d[j] ? 1.f : (w < d[j] ? -kMissWeight : 0.f);
     loss += valid ? kMissWeight * fmaxf(0.f, d[j] - w) + fmaxf(0.f, w - d[j]) : 0.f;
-    G[lane * 2 + j] = valid ? gw * blk[KFMLP_OFF_SCALE + j] * sigmoid(o[j]) : 0.f;
+    if (wv == 0) G[lane * 2 + j] = valid ? gw * blk[KFMLP_OFF_SCALE + j] * sigmoid(o[j]) : 0.f;
   }
   __syncthreads();
   // head gradients: dW3[j][k] = sum_r G[r][j] H2[r][k] (lane = k), db3
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  if (wv < 2) {
+    const int j = wv;
     float s = 0.f;
+#pragma unroll 16
     for (int r = 0; r < 64; ++r) s += G[r * 2 + j] * bf16_to_f(H2R[r * P + lane]);
     out[KFMLP_P_W3 + j * 64 + lane] = s;
     const float gb = wave_sum(G[lane * 2 + j]);
     if (lane == 0) out[KFMLP_P_B3 + j] = gb;
   }
   // dZ2 = (G W3) * gelu'(Z2), tile layout; bias gradient db2
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    const int col = nt * 16 + r16;
+  {
     const float w3a = bf16_to_f(W[KFMLP_W3 + col]), w3b = bf16_to_f(W[KFMLP_W3 + 64 + col]);
     float bsum = 0.f;
 #pragma unroll
@@ -152,7 +156,7 @@ __global__ void __launch_bounds__(64) grad_kernel(const float* __restrict__ blk,
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = mt * 16 + 4 * kq + i;
-        dz[i] = (G[r * 2] * w3a + G[r * 2 + 1] * w3b) * gelu_grad(z2[mt][nt][i]);
+        dz[i] = (G[r * 2] * w3a + G[r * 2 + 1] * w3b) * gelu_grad(z2[mt][i]);
         bsum += dz[i];
       }
       store_bf16_tile_rows(DZR, mt * 16, col, dz);
@@ -164,7 +168,8 @@ __global__ void __launch_bounds__(64) grad_kernel(const float* __restrict__ blk,
   }
   __syncthreads();
   // dW2[j][k] = sum_r dZ2[r][j] H1[r][k]
-  for (int mt = 0; mt < 4; ++mt) {
+  {
+    const int mt = wv;
     const bf16x8 a0 = load8(DZT + (mt * 16 + r16) * P + 8 * kq);
     const bf16x8 a1 = load8(DZT + (mt * 16 + r16) * P + 32 + 8 * kq);
 #pragma unroll
@@ -179,36 +184,34 @@ __global__ void __launch_bounds__(64) grad_kernel(const float* __restrict__ blk,
   // dH1 = dZ2 W2, dZ1 = dH1 * gelu'(Z1) -> XR reused as dZ1 [unit][row]
   uint16_t* DZ1T = XR;
   __syncthreads();
+  {
+    const uint16_t* b = W + KFMLP_W2T + col * 64;
+    const bf16x8 w20 = load8(b + 8 * kq), w21 = load8(b + 32 + 8 * kq);
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    const bf16x8 a0 = load8(DZR + (mt * 16 + r16) * P + 8 * kq);
-    const bf16x8 a1 = load8(DZR + (mt * 16 + r16) * P + 32 + 8 * kq);
+    for (int mt = 0; mt < 4; ++mt) {
+      f32x4 acc = mfma(load8(DZR + (mt * 16 + r16) * P + 8 * kq), w20, f32x4{0.f, 0.f, 0.f, 0.f});
+      acc = mfma(load8(DZR + (mt * 16 + r16) * P + 32 + 8 * kq), w21, acc);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const uint16_t* b = W + KFMLP_W2T + (nt * 16 + r16) * 64;
-      f32x4 acc = mfma(a0, load8(b + 8 * kq), f32x4{0.f, 0.f, 0.f, 0.f});
-      acc = mfma(a1, load8(b + 32 + 8 * kq), acc);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] *= gelu_grad(z1[mt][nt][i]);
-      z1[mt][nt] = acc;  // now dZ1
-      store_bf16_tile_cols(DZ1T, mt * 16, nt * 16 + r16, acc);
+      for (int i = 0; i < 4; ++i) acc[i] *= gelu_grad(z1[mt][i]);
+      z1[mt] = acc;  // now dZ1
+      store_bf16_tile_cols(DZ1T, mt * 16, col, acc);
     }
   }
   // db1
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
+  {
     float bsum = 0.f;
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bsum += z1[mt][nt][i];
+      for (int i = 0; i < 4; ++i) bsum += z1[mt][i];
     bsum += __shfl_xor(bsum, 16, 64);
     bsum += __shfl_xor(bsum, 32, 64);
-    if (kq == 0) out[KFMLP_P_B1 + nt * 16 + r16] = bsum;
+    if (kq == 0) out[KFMLP_P_B1 + col] = bsum;
   }
   __syncthreads();
   // dW1[j][k] = sum_r dZ1[r][j] Xh[r][k], k < 27
-  for (int mt = 0; mt < 4; ++mt) {
+  {
+    const int mt = wv;
     const bf16x8 a0 = load8(DZ1T + (mt * 16 + r16) * P + 8 * kq);
     const bf16x8 a1 = load8(DZ1T + (mt * 16 + r16) * P + 32 + 8 * kq);
 #pragma unroll
@@ -224,15 +227,25 @@ __global__ void __launch_bounds__(64) grad_kernel(const float* __restrict__ blk,
     }
   }
   const float ls = wave_sum(loss);
-  if (lane == 0) out[KFMLP_NPARAM] = ls;
+  if (threadIdx.x == 0) out[KFMLP_NPARAM] = ls;
 }
 
-// grad[p] = scale * sum over blocks (fixed order); the last entry is the loss
-__global__ void reduce_kernel(const float* __restrict__ partial, int nblk, float scale, float* __restrict__ grad) {
+// grad[p] = scale * sum over blocks (fixed order); the last entry is the loss.
+// Latency bounds it: the loads go out 16 at a time (64 blocks: 16 us one
+// after the other, 4 so), in blocks of one wave for more CUs.
+__global__ void __launch_bounds__(64) reduce_kernel(const float* __restrict__ partial, int nblk, float scale, float* __restrict__ grad) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p > KFMLP_NPARAM) return;
   float s = 0.f;
-  for (int b = 0; b < nblk; ++b) s += partial[(size_t)b * (KFMLP_NPARAM + 1) + p];
+  int b = 0;
+  for (; b + 16 <= nblk; b += 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = partial[(size_t)(b + u) * (KFMLP_NPARAM + 1) + p];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += v[u];
+  }
+  for (; b < nblk; ++b) s += partial[(size_t)b * (KFMLP_NPARAM + 1) + p];
   grad[p] = s * scale;
 }
 
@@ -325,10 +338,10 @@ extern "C" int kf_mlp_grad(const void* block, int32_t n_rows, const float* rows,
   if (!ws || ws_bytes < need) return KF_E_WORKSPACE;
   const int nblk = (n_rows + 63) / 64;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(grad_kernel, dim3(nblk), dim3(64), 0, s, (const float*)block, rows, n_rows, (float*)ws);
+  hipLaunchKernelGGL(grad_kernel, dim3(nblk), dim3(256), 0, s, (const float*)block, rows, n_rows, (float*)ws);
   if (int rc = kf_check_launch()) return rc;
   const float scale = 1.f / (2.f * (float)n_rows);
-  hipLaunchKernelGGL(reduce_kernel, dim3((KFMLP_NPARAM + 1 + 255) / 256), dim3(256), 0, s, (const float*)ws, nblk,
+  hipLaunchKernelGGL(reduce_kernel, dim3((KFMLP_NPARAM + 1 + 63) / 64), dim3(64), 0, s, (const float*)ws, nblk,
                      scale, grad);
   return kf_check_launch();
 }
