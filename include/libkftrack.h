@@ -230,7 +230,9 @@ typedef struct {
   int32_t* dump_count;        /* [1] rows written (rows beyond capacity are counted, not written) */
   int32_t dump_capacity;
   /* work counters, added to (not cleared): candidate-layers predicted, hits
-     window-tested, hits given a chi2, Kalman updates applied */
+     window-tested, hits given a chi2, Kalman updates applied.  With counters
+     every hit of a window is looked at; without, kf_build passes over hits
+     that cannot be among their seed's best (the results are the same) */
   uint64_t* counters;         /* [4] */
 } kf_build_extra;
 

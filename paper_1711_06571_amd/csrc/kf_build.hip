@@ -37,7 +37,6 @@ using namespace kfreach;
 
 namespace {
 
-
 struct BuildArgs {
   // geometry
   int n_layers;
@@ -690,14 +689,8 @@ __device__ inline int best_children(const BuildArgs& A, const Pool& po, const Gr
 #ifndef KF_LEARNED_F64_NPT
 #define KF_LEARNED_F64_NPT 2
 #endif
-#ifndef KF_F64_NPT
-#define KF_F64_NPT NP
-#endif
-#ifndef KF_F32_NPT
-#define KF_F32_NPT NP
-#endif
 template <typename T, bool LEARNED>
-constexpr int NPT_OF = (sizeof(T) == 8 && LEARNED) ? KF_LEARNED_F64_NPT : sizeof(T) == 8 ? KF_F64_NPT : KF_F32_NPT;
+constexpr int NPT_OF = (sizeof(T) == 8 && LEARNED) ? KF_LEARNED_F64_NPT : NP;
 
 template <typename T, bool LEARNED, bool HYB>
 __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES

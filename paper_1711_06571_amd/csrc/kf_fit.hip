@@ -152,7 +152,11 @@ __global__ void __launch_bounds__(256) seed_kernel(GeomK g, int n, int ld, const
 // T is the arithmetic type (float, or double for the precise mode).  HYB:
 // the state is the hybrid one (x, y, z, q/pT, phi, theta), entered from the
 // Cartesian seed and returned as it is.
-template <typename T, bool HYB>
+// AHEAD: a layer's hit is loaded one layer ahead, so the state's chain hides
+// the load (FP64 arithmetic bounds the kernel).  Both forms give the same bits
+// (tested: a form whose products the compiler contracted otherwise moved the
+// fits of ill-conditioned tracks).
+template <typename T, bool HYB, bool AHEAD>
 __global__ void __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 1)) fit_kernel(GeomK g, int n, int ld, int first_layer,
                                                   const float* __restrict__ hits,
                                                   const uint32_t* __restrict__ hole_mask,
@@ -179,9 +183,6 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 1)) fit_kernel(Geom
   T chi2 = 0;
   int ndof = 0;
   int st = (all_finite(X, 6) && all_finite(P, 21)) ? 0 : KF_NONFINITE;
-  // a layer's hit is loaded one layer ahead, so the state's chain hides the
-  // load (FP64 arithmetic bounds the kernel; 1 M tracks of 17 layers: 521 us
-  // with the load at its use, 498 so)
   float nx[9] = {};
   auto load = [&](int l) {
     if (l >= g.n_layers || ((holes >> l) & 1u)) return;
@@ -189,14 +190,21 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 1)) fit_kernel(Geom
 #pragma unroll
     for (int c = 0; c < 9; ++c) nx[c] = __builtin_nontemporal_load(hl + (size_t)c * ld);
   };
-  load(first_layer);
+  if constexpr (AHEAD) load(first_layer);
   for (int l = first_layer; l < g.n_layers && !st; ++l) {
     const bool use = !((holes >> l) & 1u);
     float hv[9];  // kept in the storage type until the update
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int c = 0; c < 9; ++c) hv[c] = nx[c];
-    if (use && !all_finite(hv, 9)) { st = KF_NONFINITE; break; }
-    load(l + 1);
+      for (int c = 0; c < 9; ++c) hv[c] = nx[c];
+      if (use && !all_finite(hv, 9)) { st = KF_NONFINITE; break; }
+      load(l + 1);
+    } else if (use) {
+      const float* hl = hits + (size_t)l * 9 * ld + i;
+#pragma unroll
+      for (int c = 0; c < 9; ++c) hv[c] = __builtin_nontemporal_load(hl + (size_t)c * ld);
+      if (!all_finite(hv, 9)) { st = KF_NONFINITE; break; }
+    }
     T Xp[6], Pp[21];
     int rc;
     if constexpr (HYB)
@@ -270,12 +278,17 @@ int fit_launch(const kf_geometry* g, int32_t n, int32_t ld, int32_t first_layer,
   if (!hits || !seed_par || !seed_cov || !q || !out_par || !out_cov || !out_chi2 || !out_ndof || !out_status)
     return KF_E_INVALID_ARG;
   const int bs = 256;
+  // Loading ahead pays where many waves share the memory (14 layers, FP64: 10 000
+  // tracks 39.3 -> 37.2 us, 1 M 414 -> 400; FP32 3 to 8 %); with few, the
+  // loads are short and the moves cost more (1 000 tracks: 35.7 -> 36.1 us,
+  // hybrid 49.4 -> 51.5).
+  const bool ahead = n >= 8192;
   if (arith == KF_ARITH_F64)
-    hipLaunchKernelGGL((fit_kernel<double, HYB>), dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g),
+    hipLaunchKernelGGL((ahead ? fit_kernel<double, HYB, true> : fit_kernel<double, HYB, false>), dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g),
                        n, ld, first_layer, hits, hole_mask, seed_par, seed_cov, q, out_par, out_cov, out_chi2,
                        out_ndof, out_status);
   else
-    hipLaunchKernelGGL((fit_kernel<float, HYB>), dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g),
+    hipLaunchKernelGGL((ahead ? fit_kernel<float, HYB, true> : fit_kernel<float, HYB, false>), dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g),
                        n, ld, first_layer, hits, hole_mask, seed_par, seed_cov, q, out_par, out_cov, out_chi2,
                        out_ndof, out_status);
   return kf_check_launch();

@@ -15,11 +15,13 @@ constexpr int NP = 2;
 //                              (FP64: only the covariance entries not in xs)
 //   record   [SEEDS][27] f32   best finished candidate of each seed
 //   recfield [SEEDS][5] i32    valid, nhits, status, last layer, slot
-//   toplist  [cap][64] f32 chi2, then [cap][64] i32 positions, [cap][64] u32 indices
 //   starts   [64 NP] i32 run starts of the cooperative hit search
-//   publish  [64] f32 chi2, [64] u32 indices of a round's admissible hits
+//   publish  [64] i32 entries of each seed's pool, [64] i32 whether one of a
+//            candidate's hits was accepted
+//   pool     [8 cap][SEEDS] of 8 B: a seed's accepted hits (chi2, position and
+//            slot), ranked and cut to cap when the next round might not fit
 //   mlp      activation buffer of the learned window (the network runs before
-//            the hit search, so the toplists of a learned build live in it)
+//            the hit search, so the pools of a learned build live in it)
 //   xs       [6 + NPL][64] f64 FP64 builds: the state between layers (below)
 // FP64 builds keep each candidate's state between layers in LDS as
 // doubles: the position and momentum and the last NPL covariance entries
