@@ -146,19 +146,21 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
   const double turns = A.n_phi / kTwoPi;
   int ln = 0, lpn = -1;
   float xn = 0.f, yn = 0.f, zn = 0.f;
-  auto load = [&](int i) {
-    if (i >= i1) return;
+  auto load = [&](int k) {
+    if (k >= i1 - i0) return;
+    const int i = i0 + k;
     ln = A.layer[i];
     lpn = i > 0 ? A.layer[i - 1] : -1;
     xn = A.xyz[i];
     yn = A.xyz[(size_t)n + i];
     zn = A.xyz[2 * (size_t)n + i];
   };
-  load(i0 + t);
-  for (int i = i0 + t; i < i1; i += 256) {
+  load(t);
+  for (int k = t; k < i1 - i0; k += 256) {
+    const int i = i0 + k;
     const int l = ln, lp = lpn;
     const float xf = xn, yf = yn, zf = zn;
-    load(i + 256);  // on its way during the arithmetic
+    load(k + 256);  // on its way during the arithmetic
     const int e = eoff ? event_of(eoff, elo, ehi, i) : 0;
     if (l < 0 || l >= L || !finite3(xf, yf, zf)) {
       A.gbin_of[i] = -1;
@@ -190,9 +192,9 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
       ok = false;
       continue;
     }
-    for (int k = fp + 1; k <= f; ++k) A.seg[k] = i;
+    for (int j = fp + 1; j <= f; ++j) A.seg[j] = i;
     if (i == n - 1)
-      for (int k = f + 1; k <= EL; ++k) A.seg[k] = n;
+      for (int j = f + 1; j <= EL; ++j) A.seg[j] = n;
   }
   if (A.try_grouped) {
     const int all_ok = __syncthreads_and(ok);
@@ -759,8 +761,10 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   if (!try_grouped)
     hipLaunchKernelGGL(clear_kernel, dim3(std::min(grid_for(NB, bs), 4096)), dim3(bs), 0, s, w.count, NB, w.ctl,
                        out_bad);
-  // pieces of a bin: a rank compares within a piece
-  const int F = try_grouped && NB < (1 << 24) ? std::max(1, kSegPieces / nb) : 1;
+  // pieces of a bin: a rank compares within a piece (all pieces of the call
+  // are numbered in 32 bits)
+  const int F =
+      try_grouped ? (int)std::max<int64_t>(1, std::min<int64_t>(kSegPieces / nb, ((1ll << 31) - 1) / NB)) : 1;
   const int blocks = std::max(1, std::min(grid_for(n_hits, bs), kBinGrid));
   BinArgs B{n_hits, n_events, L, n_phi, n_z, event_offsets, layer, xyz, w.gbin_of, w.phi_of, w.arrival, w.count, NB, F,
             w.seg, w.blk_bad, w.ctl, out_bad, whole ? 0 : 1, try_grouped ? 1 : 0};

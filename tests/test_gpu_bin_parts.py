@@ -58,3 +58,32 @@ def test_parts_of_a_range(name, seed):
         assert np.array_equal(xyzphi[3, sl], o["phi"])
         assert np.array_equal(xyzphi[:3, sl], x[:, o["order"]])
         assert np.array_equal(scov[:, sl], c[:, o["order"]])
+
+
+def test_more_ranges_than_32_bits_of_pieces():
+    """45 000 events of one bin a layer: 765 000 ranges, which 3 072 pieces
+    each would number past 32 bits.  Hits in the first, some middle and the
+    last events."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1711_06571_amd import kftrack as kf
+    g, rng, E = presets.build().geometry, np.random.default_rng(5), 45000
+    used = [0, 1, 20000, 41000, 41120, 41121, E - 1]
+    n_of = np.zeros(E, np.int64)
+    n_of[used] = 17 * 40
+    off = np.concatenate([[0], np.cumsum(n_of)]).astype(np.int32)
+    n = int(off[-1])
+    layer = np.tile(np.repeat(np.arange(17), 40), len(used)).astype(np.int32)
+    phi, r = rng.uniform(0, 2 * np.pi, n), 30.0 + 40.0 * layer
+    xyz = np.stack([r * np.cos(phi), r * np.sin(phi), rng.uniform(-1, 1, n) * g.z_half]).astype(np.float32)
+    b = kf.hit_bin(g, 1, 1, to_dev(layer), to_dev(xyz), to_dev(rng.random((6, n)).astype(np.float32)),
+                   event_offsets=to_dev(off))
+    torch.cuda.synchronize()
+    offsets, orig = host(b.offsets).reshape(E, 17, 2), host(b.orig)
+    empty = np.setdiff1d(np.arange(E), used)
+    assert np.array_equal(offsets[empty], np.broadcast_to(off[empty][:, None, None], (empty.size, 17, 2)))
+    for e in used:
+        sl = slice(off[e], off[e + 1])
+        o = oracle.hit_bin(g, 1, 1, np.ascontiguousarray(layer[sl]), np.ascontiguousarray(xyz[:, sl]))
+        assert np.array_equal(offsets[e].ravel() - off[e], np.asarray(o["offsets"]).ravel())
+        assert np.array_equal(orig[sl], o["order"])
