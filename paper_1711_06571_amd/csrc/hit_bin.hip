@@ -209,12 +209,12 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
 // generator deliver them), the hits of an (event, layer) are one contiguous
 // input range and their sorted positions are that same range.  Blocks then
 // sort the range in parts of at most `part` consecutive sorted positions (and
-// the rest of a bin), each on its own:
-//   1. an LDS histogram of the range's bins and its scan: the bin starts,
-//      hence the part's bins;
-//   2. angle and input index of the part's hits into LDS, bin by bin
-//      (arbitrary order inside a bin);
-//   3. every hit counts the hits of its bin with a smaller (phi, input
+// the rest of a piece), each on its own:
+//   1. an LDS histogram of the range's bins, each cut in F pieces of its
+//      angles, and its scan: the starts, hence the part's pieces;
+//   2. angle and input index of the part's hits into LDS, piece by piece
+//      (arbitrary order inside a piece);
+//   3. every hit counts the hits of its piece with a smaller (phi, input
 //      index) key: its sorted position, to which the pair then moves;
 //   4. one component after the other: the range read in input order into
 //      LDS, picked from there in the sorted order, written out in one piece.
@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
 // phase, bounded by LDS reads, which is why a bin is cut in pieces of its
 // angles and the angles alone are compared (5 hits a bin: 74 k cycles a block
 // with (angle, index) pairs of whole bins, 17 k so; the components 46 k).
-// 1 700 ranges of about 5 000 hits: 199 us here and 327 for the call, against
+// 1 700 ranges of about 5 000 hits: 199 us here and 311 for the call, against
 // 616 with one block per range that scattered whole records to their bins in
 // memory and read them back (214 B a hit); 340 ranges of 20 000 in three
 // parts each: 296 us here and 400 for the call, against 1 030 by the general
@@ -232,11 +232,15 @@ constexpr int kSegPer = 8;                       // positions of a part per thre
 constexpr int kSegCap = kSegPer * kSegThreads;   // positions of a part at most: two blocks' LDS on a CU
 constexpr int kSegTile = 2048;                   // hits of a bin at most
 constexpr int kSegPart = 6784;                   // leaves room for the rest of a piece
+// One event of 20 000 tracks, the whole build call: 476 us with parts of 1 024,
+// 481 with 2 048, 491 with 512 (each part reads the range's bins).
 constexpr int kSegMinPart = 1024;
 constexpr int kSegMaxBins = 4096;                // n_phi * n_z the grouped path takes: 12 bits
 constexpr int kSegIdxBits = 20;                  // an index inside the range beside the bin
-constexpr int kSegStage = 4;                     // parts of a range that still stage the whole range
-
+// Parts of a range up to which each stages the whole range; with more, a part
+// reads its own hits alone.  Build call of 20 events (three parts a range): 5.35 ms
+// staged, 5.74 not; of one event (20 parts): 476 us not staged, 500 staged.
+constexpr int kSegStage = 4;
 constexpr int kSegPieces = 3072;                 // pieces of all bins that leave two blocks their LDS
 
 size_t seg_lds_bytes(int np) { return (size_t)kSegCap * 8 + (size_t)(np + 1) * 4; }
@@ -748,16 +752,17 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   const int bs = 256;
   const int nb = n_phi * n_z;
   const int EL = n_events * L;
-  // The grouped path is tried wherever its bins fit: its launch finds out in 3 to
-  // 11 us that it does not apply (340 k shuffled hits: 5 us of 190), and where it does it is the faster from the
-  // smallest event (500 tracks: 85 us to 57) to the largest batch.  (All clearing is
+  // The grouped path is tried wherever its bins fit: it finds out in 3 to
+  // 11 us that it does not apply (340 k shuffled hits: 5 us of 190), and where
+  // it does it is the faster, from the smallest event (500 tracks: 85 us to 57)
+  // to the largest batch.  (All clearing is
   // done by kernels, not memset nodes, so the sequence can be captured.)
   const char* path = getenv("KFTRACK_HIT_BIN_PATH");
   const bool try_grouped = nb <= kSegMaxBins && !(path && !strcmp(path, "general"));
   const int cus = device_cus();
   // The reported word: 0 only where the grouped path takes whole ranges, with
   // the override or six ranges and more per CU.
-  const bool whole = path && !strcmp(path, "grouped") || EL >= 6 * cus;
+  const bool whole = (path && !strcmp(path, "grouped")) || EL >= 6 * cus;
   if (!try_grouped)
     hipLaunchKernelGGL(clear_kernel, dim3(std::min(grid_for(NB, bs), 4096)), dim3(bs), 0, s, w.count, NB, w.ctl,
                        out_bad);
