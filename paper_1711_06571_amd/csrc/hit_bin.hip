@@ -17,6 +17,9 @@
 #include <algorithm>
 
 #include "kfhost.h"
+#include "kfranges.h"
+
+using namespace kfranges;
 
 namespace {
 
@@ -34,15 +37,6 @@ __global__ void clear_kernel(int32_t* __restrict__ count, int64_t n, int32_t* __
   }
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     count[i] = 0;
-}
-
-// The event e in [lo, hi) with eoff[e] <= i < eoff[e + 1].
-__device__ inline int event_of(const int32_t* __restrict__ eoff, int lo, int hi, int i) {
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (eoff[mid] <= i) lo = mid; else hi = mid;
-  }
-  return lo;
 }
 
 // The row coordinate of each layer: w = z on a barrel layer, w = r =
@@ -111,7 +105,7 @@ struct BinArgs {
   int64_t NB;
   int32_t F;
   int32_t* seg;      // [E L + 1] first hit of every range
-  uint8_t* blk_bad;  // [kBinGrid] 1: the block's hits are not grouped, or not all valid
+  uint8_t* blk_bad;  // [kBinGrid] 1: the block's hits are not grouped or not all valid, or its events do not tile the hits
   int32_t* ctl;      // see BinWs
   int32_t* bad;      // may be null
   int32_t flag0, try_grouped;
@@ -120,6 +114,7 @@ struct BinArgs {
 __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
   const int n = A.n, E = A.E, L = A.L, nb = A.n_phi * A.n_z, EL = E * L;
   const int t = threadIdx.x;
+  bool ok = true;
   if (A.try_grouped) {
     if (blockIdx.x == 0 && t == 0) {
       A.ctl[0] = A.flag0;
@@ -131,6 +126,9 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
       A.count[k] = 0;
     if (n == 0)
       for (int k = blockIdx.x * blockDim.x + t; k <= EL; k += gridDim.x * blockDim.x) A.seg[k] = 0;
+    if (A.eoff)
+      for (int64_t e = blockIdx.x * (int64_t)blockDim.x + t; e < E; e += (int64_t)gridDim.x * blockDim.x)
+        ok = ok && tiles(A.eoff, E, n, (int)e);
   }
   // a run of hits per block, so most hits need no search for their event
   const int per = (int)((((int64_t)n + gridDim.x - 1) / gridDim.x + 255) & ~(int64_t)255);
@@ -142,7 +140,6 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
     elo = event_of(eoff, 0, E, i0);
     ehi = event_of(eoff, elo, E, i1 - 1) + 1;
   }
-  bool ok = true;
   const double turns = A.n_phi / kTwoPi;
   int ln = 0, lpn = -1;
   float xn = 0.f, yn = 0.f, zn = 0.f;
@@ -181,20 +178,7 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
       A.arrival[i] = atomicAdd(&A.count[gb], 1);
       continue;
     }
-    // the ranges that start at this hit: those after the last hit's
-    const int f = e * L + l;
-    int fp = -1;
-    if (i > 0) {
-      const int ep = eoff && i - 1 < eoff[e] ? event_of(eoff, 0, e + 1, i - 1) : e;
-      fp = ep * L + lp;
-    }
-    if (lp < -1 || lp >= L || f < fp) {
-      ok = false;
-      continue;
-    }
-    for (int j = fp + 1; j <= f; ++j) A.seg[j] = i;
-    if (i == n - 1)
-      for (int j = f + 1; j <= EL; ++j) A.seg[j] = n;
+    ok = range_starts(eoff, E, L, n, i, e, l, lp, A.seg) && ok;
   }
   if (A.try_grouped) {
     const int all_ok = __syncthreads_and(ok);
@@ -301,16 +285,10 @@ __global__ void __launch_bounds__(kSegThreads, 8) seg_kernel(SegArgs A) {
     if (lane == 0) s_sg = r;
   }
   for (int k = t; k <= np; k += kSegThreads) start[k] = 0;
-  // (without a bad block every entry of seg is written, ascending in [0, n];
-  // the events must tile [0, n) too)
+  // (without a bad block every entry of seg is written, ascending in [0, n])
   if (__syncthreads_or(bad)) {
     if (t == 0) A.ctl[0] = A.ctl[1] = 1;
     return;
-  }
-  if (t == 0 && b < EL && A.eoff) {
-    const int e = b / A.L, e0 = A.eoff[e], e1 = A.eoff[e + 1];
-    if (e0 < 0 || e1 < e0 || e1 > A.n || (e == 0 && e0 != 0) || (e == A.E - 1 && e1 != A.n) || A.seg[e * A.L] != e0)
-      A.ctl[0] = A.ctl[1] = 1;
   }
   const int sg = s_sg;
   const int a = A.seg[sg], len = A.seg[sg + 1] - a, k = b - (a / A.part + sg);
