@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(kPrepThreads)
       for (int p = first + t; p < re; p += kPrepThreads) {
         const int k = fine_key(phi[p], inv, nf) - kb;
         if (k >= m) break;  // keys do not decrease along the row
-        atomicAdd(&cnt[k], 1);
+        if (k >= 0) atomicAdd(&cnt[k], 1);  // (in a caller's row that is not in order they may)
       }
       __syncthreads();
       // exclusive scan of the counts: each wave takes a run of whole rounds
