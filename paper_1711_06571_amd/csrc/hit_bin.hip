@@ -736,8 +736,11 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   // to the largest batch.  (All clearing is
   // done by kernels, not memset nodes, so the sequence can be captured.)
   const char* path = getenv("KFTRACK_HIT_BIN_PATH");
-  const bool try_grouped = nb <= kSegMaxBins && !(path && !strcmp(path, "general"));
   const int cus = device_cus();
+  // parts that give every CU about two blocks, but not below kSegMinPart
+  const int part = std::min(kSegPart, std::max(kSegMinPart, n_hits / (2 * cus)));
+  const int64_t seg_blocks = part_blocks(n_hits, part, EL, kSegThreads);
+  const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !(path && !strcmp(path, "general"));
   // The reported word: 0 only where the grouped path takes whole ranges, with
   // the override or six ranges and more per CU.
   const bool whole = (path && !strcmp(path, "grouped")) || EL >= 6 * cus;
@@ -753,11 +756,9 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
             w.seg, w.blk_bad, w.ctl, out_bad, whole ? 0 : 1, try_grouped ? 1 : 0};
   hipLaunchKernelGGL(bin_kernel, dim3(blocks), dim3(bs), 0, s, B, rg);
   if (try_grouped) {
-    // parts that give every CU about two blocks, but not below kSegMinPart
-    const int part = std::min(kSegPart, std::max(kSegMinPart, n_hits / (2 * cus)));
     SegArgs G{n_hits, n_events, L, nb, F, part, blocks, event_offsets, w.seg, w.blk_bad, w.gbin_of, w.phi_of, xyz, cov,
               w.ctl, offsets, sorted_xyzphi, sorted_cov, sorted_orig};
-    hipLaunchKernelGGL(seg_kernel, dim3(n_hits / part + EL), dim3(kSegThreads), seg_lds_bytes(nb * F), s, G);
+    hipLaunchKernelGGL(seg_kernel, dim3((unsigned)seg_blocks), dim3(kSegThreads), seg_lds_bytes(nb * F), s, G);
     // general path from here (every kernel returns at once unless it is to run)
     if (n_hits > 0)
       hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(bs), 0, s, n_hits, F, w.gbin_of, w.arrival, w.count, out_bad,

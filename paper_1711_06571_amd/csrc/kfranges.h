@@ -44,4 +44,12 @@ KFG bool range_starts(const int32_t* eoff, int E, int L, int n, int i, int e, in
   return true;
 }
 
+// Blocks of a grouped sort: every range owns at least as many as it has parts
+// of `part` hits (the ranges tile the n hits).  -1 where the launch, of
+// `threads` threads each, would reach the 2^32 threads a grid may have.
+inline int64_t part_blocks(int n, int part, int64_t ranges, int threads) {
+  const int64_t blocks = (int64_t)(n / part) + ranges;
+  return blocks * threads < (int64_t)1 << 32 ? blocks : -1;
+}
+
 }  // namespace kfranges

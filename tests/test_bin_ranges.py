@@ -120,3 +120,31 @@ def test_no_unflagged_input_leaves_a_range_start_unwritten(tmp_path):
     assert unsound == 0 and refused == 0, r
     assert unflagged > 20000 and flagged > 20000, r
     assert missed_without > 0, r  # (the hits' order alone does not tell)
+
+
+def test_grid_of_a_grouped_sort_stays_in_bounds(tmp_path):
+    """part_blocks: the blocks of every call whose launch stays below 2^32
+    threads, -1 at and above (a product in 32 bits would wrap there)."""
+    if not os.path.exists(HIPCC) and not shutil.which("hipcc"):
+        pytest.skip("hipcc not available")
+    (tmp_path / "g.hip").write_text(r"""
+#include <cstdio>
+#include "kfranges.h"
+int main() {
+  const long long R[] = {1, 17, 4194302, 4194303, 4194304, 4250000, 8388607, 1ll << 30, (1ll << 31) - 2};
+  const int N[] = {0, 1023, 1024, 2147483647};
+  for (long long r : R) for (int n : N) for (int t : {256, 1024})
+    printf("%lld %d %d %lld\n", r, n, t, (long long)kfranges::part_blocks(n, 1024, r, t));
+}
+""")
+    subprocess.run([HIPCC, "-O1", "-std=c++17", "--cuda-host-only", "-w", "-I",
+                    os.path.join(ROOT, "paper_1711_06571_amd", "csrc"), str(tmp_path / "g.hip"), "-o",
+                    str(tmp_path / "g")], check=True, capture_output=True)
+    lines = subprocess.run([str(tmp_path / "g")], check=True, capture_output=True, text=True).stdout.splitlines()
+    refused = 0
+    for line in lines:
+        r, n, t, got = map(int, line.split())
+        blocks = n // 1024 + r
+        assert got == (blocks if blocks * t < 2 ** 32 else -1), line
+        refused += got < 0
+    assert 0 < refused < len(lines)

@@ -36,3 +36,31 @@ def test_offsets_that_do_not_tile(eoff, monkeypatch):
     assert off.min() == 0 and off.max() == n and np.all(np.diff(off.ravel()) >= 0)
     got, ref = host(b.xyzphi)[:3], xyz
     assert np.array_equal(got[:, np.lexsort(got)], ref[:, np.lexsort(ref)])
+
+
+def test_more_ranges_than_a_grid_of_parts_holds():
+    """250 000 events of 17 layers, one bin each: 4.25 M ranges, which a block
+    of 1 024 threads each would take past 2^32 threads."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1711_06571_amd import kftrack as kf
+    g, E = presets.barrel(17), 250000
+    off = (np.arange(E + 1) // 1000 * 40).astype(np.int32)  # 40 hits in every thousandth event
+    n = int(off[-1])
+    rng = np.random.default_rng(2)
+    layer = np.sort(rng.integers(0, 17, (n // 40, 40)), axis=1).astype(np.int32).ravel()
+    phi = rng.uniform(0, 2 * np.pi, n)
+    r = 4.0 * (layer + 1)
+    xyz = np.stack([r * np.cos(phi), r * np.sin(phi), rng.uniform(-90, 90, n)]).astype(np.float32)
+    b = kf.hit_bin(g, 1, 1, to_dev(layer), to_dev(xyz), to_dev(rng.random((6, n)).astype(np.float32)),
+                   event_offsets=to_dev(off))
+    torch.cuda.synchronize()
+    phi64 = np.arctan2(xyz[1].astype(np.float64), xyz[0].astype(np.float64))
+    phi32 = np.where(phi64 < 0, phi64 + 2 * np.pi, phi64).astype(np.float32)
+    ev = np.repeat(np.arange(n // 40) * 1000 + 999, 40)
+    order = np.lexsort((phi32, layer, ev))
+    assert np.array_equal(host(b.xyzphi)[:3], xyz[:, order])
+    assert np.array_equal(host(b.orig), order - off[ev[order]])
+    counts = np.bincount(ev.astype(np.int64) * 17 + layer, minlength=E * 17)
+    start = np.concatenate([[0], np.cumsum(counts)])
+    assert np.array_equal(host(b.offsets).reshape(-1, 2), np.stack([start[:-1], start[1:]], 1))
