@@ -582,13 +582,65 @@ __global__ void __launch_bounds__(256) place_kernel(int n, int F, const int32_t*
   }
 }
 
-// Exact order inside each bin: rank = number of hits of the bin with a
-// smaller (phi, original index) key.  G lanes per bin: each holds one hit
-// record of the bin and compares it with every hit of the bin, whose keys the
-// group passes around by shuffles G at a time (larger bins loop over blocks
-// of G).  The hit is then written to its slot in the sorted arrays.
-// 8.16 M hits, 5 a bin: 500 us with 64 lanes a bin, 454 with 16; 20 a bin:
-// 790 us with 32 lanes, 613 with 64.
+// Exact order inside a bin: rank = number of hits of the bin with a smaller
+// (phi, original index) key.  W lanes (lane: this one's index among them) each
+// hold one hit record of the bin and compare it with every hit of the bin,
+// whose keys they pass around W at a time (larger bins loop over blocks of
+// W).  The hit is then written to its slot in the sorted arrays.
+template <int W>
+__device__ inline void rank_bin(int lane, int b0, int cnt, int ev_base, size_t N, const float4* __restrict__ rec,
+                                float* __restrict__ sorted_xyzphi, float* __restrict__ sorted_cov,
+                                int32_t* __restrict__ sorted_orig) {
+  for (int c0 = 0; c0 < cnt; c0 += W) {
+    const bool mine = c0 + lane < cnt;
+    const float4* r = rec + (size_t)(b0 + c0 + (mine ? lane : 0)) * 3;
+    const float4 r0 = r[0], r1 = r[1], r2 = r[2];
+    const int i = __float_as_int(r2.z);
+    const float ph = r0.w;
+    int rank = 0;
+    // the keys of the next W hits are on their way during the comparisons
+    float np = 0.f;
+    int ni = 0;
+    auto load = [&](int d0) {
+      const float4* o = rec + (size_t)(b0 + (d0 + lane < cnt ? d0 + lane : 0)) * 3;
+      ni = __float_as_int(o[2].z);
+      np = o[0].w;
+    };
+    if (cnt > W) load(0);
+    for (int d0 = 0; d0 < cnt; d0 += W) {
+      const int oi = cnt > W ? ni : i;
+      const float op = cnt > W ? np : ph;
+      if (d0 + W < cnt) load(d0 + W);
+      const int m = cnt - d0 < W ? cnt - d0 : W;
+      for (int t = 0; t < m; ++t) {
+        const float pj = __shfl(op, t, W);
+        const int j = __shfl(oi, t, W);
+        rank += (pj < ph || (pj == ph && j < i)) ? 1 : 0;
+      }
+    }
+    if (mine) {
+      const int dst = b0 + rank;
+      sorted_xyzphi[dst] = r0.x;
+      sorted_xyzphi[N + dst] = r0.y;
+      sorted_xyzphi[2 * N + dst] = r0.z;
+      sorted_xyzphi[3 * N + dst] = ph;
+      sorted_cov[dst] = r1.x;
+      sorted_cov[N + dst] = r1.y;
+      sorted_cov[2 * N + dst] = r1.z;
+      sorted_cov[3 * N + dst] = r1.w;
+      sorted_cov[4 * N + dst] = r2.x;
+      sorted_cov[5 * N + dst] = r2.y;
+      sorted_orig[dst] = i - ev_base;
+    }
+  }
+}
+
+// G lanes per bin, 64 / G bins at once; where one of these bins is so much
+// the largest that the others' lanes would mostly wait for it, all 64 lanes
+// take the bins one after another (85 000 shuffled hits, a bin of 1 000 a layer:
+// 5 239 us with G lanes alone, 1 003 so; 20 bins of 100 a layer: 122 and 72).
+// 8.16 M hits, 5 a bin: 500 us with 64 lanes a bin, 454 with 16; 20 a bin: 790
+// us with 32 lanes, 613 with 64.
 template <int G>
 __global__ void __launch_bounds__(256) rank_kernel(int NB, int n, int L, int nb_el,
                                                    const int32_t* __restrict__ eoff,
@@ -600,48 +652,30 @@ __global__ void __launch_bounds__(256) rank_kernel(int NB, int n, int L, int nb_
                                                    float* __restrict__ sorted_cov, int32_t* __restrict__ sorted_orig,
                                                    const int32_t* __restrict__ go) {
   if (*go == 0) return;
-  const int lane = threadIdx.x % G;
-  const int64_t groups = gridDim.x * (int64_t)(blockDim.x / G);
-  for (int64_t gb = blockIdx.x * (int64_t)(blockDim.x / G) + threadIdx.x / G; gb < NB; gb += groups) {
-    const int cnt = count[gb];
-    if (cnt == 0) continue;
-    const int b0 = bin_start(start, bsum, gb);
+  const int lane = threadIdx.x & 63, sub = lane / G;
+  const int64_t waves = gridDim.x * (int64_t)(blockDim.x / 64);
+  for (int64_t g0 = (blockIdx.x * (int64_t)(blockDim.x / 64) + threadIdx.x / 64) * (64 / G); g0 < NB;
+       g0 += waves * (64 / G)) {
+    const int64_t gb = g0 + sub;
+    const int cnt = gb < NB ? count[gb] : 0;
+    if (!__any(cnt > 0)) continue;
+    const int b0 = cnt > 0 ? bin_start(start, bsum, gb) : 0;
     // the event of the bin: bins are numbered (event * L + layer) * nb_el + bin
-    const int ev_base = eoff ? eoff[gb / (L * nb_el)] : 0;
-    for (int c0 = 0; c0 < cnt; c0 += G) {
-      const bool mine = c0 + lane < cnt;
-      const float4* r = rec + (size_t)(b0 + c0 + (mine ? lane : 0)) * 3;
-      const float4 r0 = r[0], r1 = r[1], r2 = r[2];
-      const int i = __float_as_int(r2.z);
-      const float ph = r0.w;
-      int rank = 0;
-      for (int d0 = 0; d0 < cnt; d0 += G) {
-        const bool theirs = d0 + lane < cnt;
-        const float4* o = rec + (size_t)(b0 + d0 + (theirs ? lane : 0)) * 3;
-        const int oi = d0 == c0 ? i : __float_as_int(o[2].z);
-        const float op = d0 == c0 ? ph : o[0].w;
-        const int m = cnt - d0 < G ? cnt - d0 : G;
-        for (int t = 0; t < m; ++t) {
-          const float pj = __shfl(op, t, G);
-          const int j = __shfl(oi, t, G);
-          rank += (pj < ph || (pj == ph && j < i)) ? 1 : 0;
-        }
-      }
-      if (mine) {
-        const int dst = b0 + rank;
-        const size_t N = (size_t)n;
-        sorted_xyzphi[dst] = r0.x;
-        sorted_xyzphi[N + dst] = r0.y;
-        sorted_xyzphi[2 * N + dst] = r0.z;
-        sorted_xyzphi[3 * N + dst] = ph;
-        sorted_cov[dst] = r1.x;
-        sorted_cov[N + dst] = r1.y;
-        sorted_cov[2 * N + dst] = r1.z;
-        sorted_cov[3 * N + dst] = r1.w;
-        sorted_cov[4 * N + dst] = r2.x;
-        sorted_cov[5 * N + dst] = r2.y;
-        sorted_orig[dst] = i - ev_base;
-      }
+    const int ev_base = cnt > 0 && eoff ? eoff[gb / (L * nb_el)] : 0;
+    // the steps of a wave: the largest bin's with G lanes a bin, the sum with 64
+    float together = (float)((cnt + G - 1) / G) * (float)cnt, alone = (float)((cnt + 63) / 64) * (float)cnt;
+#pragma unroll
+    for (int d = G; d < 64; d <<= 1) {
+      together = fmaxf(together, __shfl_xor(together, d, 64));
+      alone += __shfl_xor(alone, d, 64);
+    }
+    if (G == 64 || together <= alone) {
+      rank_bin<G>(lane % G, b0, cnt, ev_base, (size_t)n, rec, sorted_xyzphi, sorted_cov, sorted_orig);
+    } else {
+#pragma unroll 1
+      for (int j = 0; j < 64; j += G)
+        rank_bin<64>(lane, __builtin_amdgcn_readlane(b0, j), __builtin_amdgcn_readlane(cnt, j),
+                     __builtin_amdgcn_readlane(ev_base, j), (size_t)n, rec, sorted_xyzphi, sorted_cov, sorted_orig);
     }
   }
 }
