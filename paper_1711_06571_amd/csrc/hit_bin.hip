@@ -208,17 +208,20 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
 // with (angle, index) pairs of whole bins, 17 k so; the components 46 k).
 // 1 700 ranges of about 5 000 hits: 199 us here and 311 for the call, against
 // 616 with one block per range that scattered whole records to their bins in
-// memory and read them back (214 B a hit); 340 ranges of 20 000 in three
-// parts each: 296 us here and 400 for the call, against 1 030 by the general
-// path.  A longer prefetch (18 loads a thread) changed nothing.
-constexpr int kSegThreads = 1024;
-constexpr int kSegPer = 8;                       // positions of a part per thread
-constexpr int kSegCap = kSegPer * kSegThreads;   // positions of a part at most: two blocks' LDS on a CU
+// memory and read them back (214 B a hit); 408 ranges of 20 000 in three
+// parts each: 400 us for the call, against 876 by the general path then.  A longer prefetch (18 loads a thread) changed nothing.
+constexpr int kSegPer = 8;                       // positions of a part per thread, at most
 constexpr int kSegTile = 2048;                   // hits of a bin at most
 constexpr int kSegPart = 6784;                   // leaves room for the rest of a piece
 // One event of 20 000 tracks, the whole build call: 476 us with parts of 1 024,
 // 481 with 2 048, 491 with 512 (each part reads the range's bins).
 constexpr int kSegMinPart = 1024;
+// Ranges of up to this many hits in the mean are sorted by blocks of 256
+// threads, five to seven on a CU: 1 024 threads spend 25 us on a range of any
+// size (17 408 ranges of 150 hits: 862 us, 286 with 256 threads; 1 088 ranges
+// of 1 500: 100 and 79, of 3 000: 134 and 203).
+constexpr int kSegSmall = 2000;
+constexpr int kSegSmallPart = 1664;
 constexpr int kSegMaxBins = 4096;                // n_phi * n_z the grouped path takes: 12 bits
 constexpr int kSegIdxBits = 20;                  // an index inside the range beside the bin
 // Parts of a range up to which each stages the whole range; with more, a part
@@ -227,7 +230,7 @@ constexpr int kSegIdxBits = 20;                  // an index inside the range be
 constexpr int kSegStage = 4;
 constexpr int kSegPieces = 3072;                 // pieces of all bins that leave two blocks their LDS
 
-size_t seg_lds_bytes(int np) { return (size_t)kSegCap * 8 + (size_t)(np + 1) * 4; }
+size_t seg_lds_bytes(int threads, int np) { return (size_t)(kSegPer * threads) * 8 + (size_t)(np + 1) * 4; }
 
 struct SegArgs {
   int n, E, L, nb, F, part, n_blk;
@@ -262,7 +265,9 @@ __device__ inline int range_of_block(const int32_t* __restrict__ seg, int EL, in
 // a / part + s at or below b (a: the range's first hit): the ranges tile the
 // input, so every range owns at least as many blocks as it has parts, and
 // n / part + E L blocks hold them all.
-__global__ void __launch_bounds__(kSegThreads, 8) seg_kernel(SegArgs A) {
+template <int T>
+__global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
+  constexpr int kSegThreads = T, kSegCap = kSegPer * T;
   extern __shared__ __align__(16) int32_t sm[];
   float* key = (float*)sm;                 // [kSegCap] angle, then the staged component
   uint32_t* idx = (uint32_t*)sm + kSegCap; // [kSegCap] (piece, input index in the range), then the index alone
@@ -275,10 +280,10 @@ __global__ void __launch_bounds__(kSegThreads, 8) seg_kernel(SegArgs A) {
   const int per_xcd = (int)gridDim.x / 8;
   const int b = (int)blockIdx.x < per_xcd * 8 ? (int)(blockIdx.x % 8) * per_xcd + (int)blockIdx.x / 8 : (int)blockIdx.x;
   bool bad = false;
-  if (t < (A.n_blk + 3) / 4) {
-    const int left = A.n_blk - 4 * t;
-    const uint32_t w = ((const uint32_t*)A.blk_bad)[t];
-    bad = (left >= 4 ? w : w & ((1u << (8 * left)) - 1)) != 0;
+  for (int k = t; k < (A.n_blk + 3) / 4; k += kSegThreads) {
+    const int left = A.n_blk - 4 * k;
+    const uint32_t w = ((const uint32_t*)A.blk_bad)[k];
+    bad = bad || (left >= 4 ? w : w & ((1u << (8 * left)) - 1)) != 0;
   }
   if (t >= kSegThreads - 64) {
     const int r = range_of_block(A.seg, EL, A.part, b, lane);
@@ -294,6 +299,11 @@ __global__ void __launch_bounds__(kSegThreads, 8) seg_kernel(SegArgs A) {
   const int a = A.seg[sg], len = A.seg[sg + 1] - a, k = b - (a / A.part + sg);
   const int parts = len > A.part ? (len + A.part - 1) / A.part : 1;
   if (k >= parts) return;
+  if (len == 0) {
+    int32_t* off = A.offsets + (size_t)sg * (A.nb + 1);
+    for (int q = t; q <= A.nb; q += kSegThreads) off[q] = a;
+    return;
+  }
   if (len >= 1 << kSegIdxBits) {
     if (t == 0) A.ctl[0] = A.ctl[1] = 1;
     return;
@@ -764,16 +774,19 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   const int bs = 256;
   const int nb = n_phi * n_z;
   const int EL = n_events * L;
+  const char* path = getenv("KFTRACK_HIT_BIN_PATH");
+  const int cus = device_cus();
+  const int64_t mean = n_hits / EL;  // hits of a range
+  const bool small = mean <= kSegSmall;
+  const int threads = small ? 256 : 1024;
+  // parts that give every CU about two blocks, but not below kSegMinPart
+  const int part = small ? kSegSmallPart : std::min(kSegPart, std::max(kSegMinPart, n_hits / (2 * cus)));
+  const int64_t seg_blocks = part_blocks(n_hits, part, EL, threads);
   // The grouped path is tried wherever its bins fit: it finds out in 3 to
   // 11 us that it does not apply (340 k shuffled hits: 5 us of 190), and where
   // it does it is the faster, from the smallest event (500 tracks: 85 us to 57)
   // to the largest batch.  (All clearing is
   // done by kernels, not memset nodes, so the sequence can be captured.)
-  const char* path = getenv("KFTRACK_HIT_BIN_PATH");
-  const int cus = device_cus();
-  // parts that give every CU about two blocks, but not below kSegMinPart
-  const int part = std::min(kSegPart, std::max(kSegMinPart, n_hits / (2 * cus)));
-  const int64_t seg_blocks = part_blocks(n_hits, part, EL, kSegThreads);
   const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !(path && !strcmp(path, "general"));
   // The reported word: 0 only where the grouped path takes whole ranges, with
   // the override or six ranges and more per CU.
@@ -781,10 +794,11 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   if (!try_grouped)
     hipLaunchKernelGGL(clear_kernel, dim3(std::min(grid_for(NB, bs), 4096)), dim3(bs), 0, s, w.count, NB, w.ctl,
                        out_bad);
-  // pieces of a bin: a rank compares within a piece (all pieces of the call
-  // are numbered in 32 bits)
-  const int F =
-      try_grouped ? (int)std::max<int64_t>(1, std::min<int64_t>(kSegPieces / nb, ((1ll << 31) - 1) / NB)) : 1;
+  // pieces of a bin: a rank compares within a piece, two for every hit of the
+  // mean bin (each piece costs a range its scan; all pieces of the call are
+  // numbered in 32 bits)
+  const int64_t pieces = std::min(std::min<int64_t>(kSegPieces / nb, ((1ll << 31) - 1) / NB), 2 * mean / nb + 1);
+  const int F = try_grouped ? (int)std::max<int64_t>(1, pieces) : 1;
   const int blocks = std::max(1, std::min(grid_for(n_hits, bs), kBinGrid));
   BinArgs B{n_hits, n_events, L, n_phi, n_z, event_offsets, layer, xyz, w.gbin_of, w.phi_of, w.arrival, w.count, NB, F,
             w.seg, w.blk_bad, w.ctl, out_bad, whole ? 0 : 1, try_grouped ? 1 : 0};
@@ -792,7 +806,8 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   if (try_grouped) {
     SegArgs G{n_hits, n_events, L, nb, F, part, blocks, event_offsets, w.seg, w.blk_bad, w.gbin_of, w.phi_of, xyz, cov,
               w.ctl, offsets, sorted_xyzphi, sorted_cov, sorted_orig};
-    hipLaunchKernelGGL(seg_kernel, dim3((unsigned)seg_blocks), dim3(kSegThreads), seg_lds_bytes(nb * F), s, G);
+    hipLaunchKernelGGL(small ? seg_kernel<256> : seg_kernel<1024>, dim3((unsigned)seg_blocks), dim3(threads),
+                       seg_lds_bytes(threads, nb * F), s, G);
     // general path from here (every kernel returns at once unless it is to run)
     if (n_hits > 0)
       hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(bs), 0, s, n_hits, F, w.gbin_of, w.arrival, w.count, out_bad,
@@ -807,8 +822,8 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
                      offsets, w.ctl + 1);
   if (n_hits > 0) {
     // lanes per bin by the mean bin
-    const int64_t mean = n_hits / NB;
-    const int G = mean < 8 ? 16 : (mean < 16 ? 32 : 64);
+    const int64_t in_bin = n_hits / NB;
+    const int G = in_bin < 8 ? 16 : (in_bin < 16 ? 32 : 64);
     auto* rank = G == 16 ? rank_kernel<16> : (G == 32 ? rank_kernel<32> : rank_kernel<64>);
     hipLaunchKernelGGL(rank, dim3(std::min(grid_for(NB * G, bs), kWideGrid)), dim3(bs), 0, s, (int)NB, n_hits, L, nb,
                        event_offsets, w.rec, w.start, w.bsum, w.count, sorted_xyzphi, sorted_cov, sorted_orig,
