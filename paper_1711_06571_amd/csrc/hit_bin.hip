@@ -31,8 +31,8 @@ constexpr int kWideGrid = 2048;   // blocks of the grid-stride kernels: eight pe
 __global__ void clear_kernel(int32_t* __restrict__ count, int64_t n, int32_t* __restrict__ ctl,
                              int32_t* __restrict__ bad) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctl[0] = ctl[1] = 1;
-    ctl[2] = 0;
+    ctl[0] = 1;
+    ctl[1] = 0;
     if (bad) *bad = 0;
   }
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -108,7 +108,7 @@ struct BinArgs {
   uint8_t* blk_bad;  // [kBinGrid] 1: the block's hits are not grouped or not all valid, or its events do not tile the hits
   int32_t* ctl;      // see BinWs
   int32_t* bad;      // may be null
-  int32_t flag0, try_grouped;
+  int32_t try_grouped;
 };
 
 __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
@@ -117,9 +117,8 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
   bool ok = true;
   if (A.try_grouped) {
     if (blockIdx.x == 0 && t == 0) {
-      A.ctl[0] = A.flag0;
+      A.ctl[0] = 0;
       A.ctl[1] = 0;
-      A.ctl[2] = 0;
       if (A.bad) *A.bad = 0;
     }
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + t; k < A.NB; k += (int64_t)gridDim.x * blockDim.x)
@@ -292,7 +291,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
   for (int k = t; k <= np; k += kSegThreads) start[k] = 0;
   // (without a bad block every entry of seg is written, ascending in [0, n])
   if (__syncthreads_or(bad)) {
-    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
+    if (t == 0) A.ctl[0] = 1;
     return;
   }
   const int sg = s_sg;
@@ -305,7 +304,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
     return;
   }
   if (len >= 1 << kSegIdxBits) {
-    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
+    if (t == 0) A.ctl[0] = 1;
     return;
   }
   const int32_t* gb = A.gbin_of + a;
@@ -346,7 +345,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
   bad = false;
   for (int q = t; q < A.nb; q += kSegThreads) bad = bad || start[(q + 1) * A.F] - start[q * A.F] > kSegTile;
   if (__syncthreads_or(bad)) {
-    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
+    if (t == 0) A.ctl[0] = 1;
     return;
   }
   if (k == 0) {
@@ -368,7 +367,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
   __syncthreads();  // (the starts move below)
   if (m <= 0) return;
   if (m > kSegCap) {
-    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
+    if (t == 0) A.ctl[0] = 1;
     return;
   }
   for (int j0 = t; j0 < len; j0 += kSegThreads * U) {
@@ -695,7 +694,7 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct BinWs {
   int32_t *gbin_of, *arrival, *count, *start, *bsum, *seg;
   uint8_t* blk_bad;
-  // [0] the reported path, [1] go: the general path runs, [2] the scan's ticket
+  // [0] the path: 1 where the general path runs, [1] the scan's ticket
   int32_t* ctl;
   float* phi_of;
   float4* rec;  // [n][3] hit records in bin slots
@@ -719,7 +718,7 @@ size_t bin_ws_layout(int E, int L, int n_phi, int n_z, int n, char* base, BinWs*
   char* g = take(sizeof(int32_t) * (nblk + 1));
   char* k = take(sizeof(int32_t) * ((size_t)E * L + 1));
   char* m = take(kBinGrid);
-  char* h = take(sizeof(int32_t) * 3);
+  char* h = take(sizeof(int32_t) * 2);
   if (w) {
     w->ctl = (int32_t*)h;
     w->seg = (int32_t*)k;
@@ -782,15 +781,21 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   // parts that give every CU about two blocks, but not below kSegMinPart
   const int part = small ? kSegSmallPart : std::min(kSegPart, std::max(kSegMinPart, n_hits / (2 * cus)));
   const int64_t seg_blocks = part_blocks(n_hits, part, EL, threads);
-  // The grouped path is tried wherever its bins fit: it finds out in 3 to
-  // 11 us that it does not apply (340 k shuffled hits: 5 us of 190), and where
-  // it does it is the faster, from the smallest event (500 tracks: 85 us to 57)
-  // to the largest batch.  (All clearing is
-  // done by kernels, not memset nodes, so the sequence can be captured.)
-  const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !(path && !strcmp(path, "general"));
-  // The reported word: 0 only where the grouped path takes whole ranges, with
-  // the override or six ranges and more per CU.
-  const bool whole = (path && !strcmp(path, "grouped")) || EL >= 6 * cus;
+  // Which path, where the input is ordered and its bins fit.  The grouped path
+  // needs ranges for half the CUs, and enough work in each: a range costs it
+  // 10 ns and 6 ps a bin, the general path 20 ps a bin and up to 0.3 ns a hit
+  // (17 layers, 1 008 bins; general against grouped, us: 1 event of 20 000
+  // tracks 57 to 58, of 60 000 128 to 153, 16 events 680 to 321, 64 events of 600
+  // hits a layer 128 to 49, 1 024 events of 2 hits a layer 355 to 234; with 16
+  // bins, 4 096 events of 40 hits a layer 279 to 738).  With fewer ranges it
+  // pays where large bins make the general path's rank slow (one event, 16 bins
+  // of 190 hits: 86 to 35; four, 252 bins of 240: 703 to 516), with many bins
+  // only where they are that large that the parts' reads of their whole range
+  // are less (one event, 1 008 bins of 200: 605 to 696, of 500: 2 598 to 2 033).
+  const int64_t in_bin = mean / nb;
+  const bool choice = in_bin >= (nb <= 512 ? 48 : 480) || (EL >= cus / 2 && nb + 4 * mean >= 640);
+  const bool forced = path && !strcmp(path, "grouped"), barred = path && !strcmp(path, "general");
+  const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !barred && (forced || choice);
   if (!try_grouped)
     hipLaunchKernelGGL(clear_kernel, dim3(std::min(grid_for(NB, bs), 4096)), dim3(bs), 0, s, w.count, NB, w.ctl,
                        out_bad);
@@ -801,7 +806,7 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   const int F = try_grouped ? (int)std::max<int64_t>(1, pieces) : 1;
   const int blocks = std::max(1, std::min(grid_for(n_hits, bs), kBinGrid));
   BinArgs B{n_hits, n_events, L, n_phi, n_z, event_offsets, layer, xyz, w.gbin_of, w.phi_of, w.arrival, w.count, NB, F,
-            w.seg, w.blk_bad, w.ctl, out_bad, whole ? 0 : 1, try_grouped ? 1 : 0};
+            w.seg, w.blk_bad, w.ctl, out_bad, try_grouped ? 1 : 0};
   hipLaunchKernelGGL(bin_kernel, dim3(blocks), dim3(bs), 0, s, B, rg);
   if (try_grouped) {
     SegArgs G{n_hits, n_events, L, nb, F, part, blocks, event_offsets, w.seg, w.blk_bad, w.gbin_of, w.phi_of, xyz, cov,
@@ -811,23 +816,22 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
     // general path from here (every kernel returns at once unless it is to run)
     if (n_hits > 0)
       hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(bs), 0, s, n_hits, F, w.gbin_of, w.arrival, w.count, out_bad,
-                         w.ctl + 1);
+                         w.ctl);
   }
   const int nblk = (int)((NB + 2 * kScanBlock - 1) / (2 * kScanBlock));
-  hipLaunchKernelGGL(scan_kernel, dim3(nblk), dim3(kScanBlock), 0, s, w.count, w.start, w.bsum, (int)NB, w.ctl + 1,
-                     w.ctl + 2);
+  hipLaunchKernelGGL(scan_kernel, dim3(nblk), dim3(kScanBlock), 0, s, w.count, w.start, w.bsum, (int)NB, w.ctl,
+                     w.ctl + 1);
   const int64_t items = std::max((int64_t)n_hits, (int64_t)EL * (nb + 1));
   hipLaunchKernelGGL(place_kernel, dim3((int)std::min<int64_t>((items + bs - 1) / bs, kWideGrid)), dim3(bs), 0, s,
                      n_hits, F, w.gbin_of, w.phi_of, w.arrival, xyz, cov, w.start, w.bsum, w.count, EL, nb, w.rec,
-                     offsets, w.ctl + 1);
+                     offsets, w.ctl);
   if (n_hits > 0) {
     // lanes per bin by the mean bin
-    const int64_t in_bin = n_hits / NB;
     const int G = in_bin < 8 ? 16 : (in_bin < 16 ? 32 : 64);
     auto* rank = G == 16 ? rank_kernel<16> : (G == 32 ? rank_kernel<32> : rank_kernel<64>);
     hipLaunchKernelGGL(rank, dim3(std::min(grid_for(NB * G, bs), kWideGrid)), dim3(bs), 0, s, (int)NB, n_hits, L, nb,
                        event_offsets, w.rec, w.start, w.bsum, w.count, sorted_xyzphi, sorted_cov, sorted_orig,
-                       w.ctl + 1);
+                       w.ctl);
   }
   return kf_check_launch();
 }
