@@ -97,13 +97,6 @@ template <typename T, typename U> __device__ inline U kv64(U v) {
   else return v;
 }
 
-// LDS accesses before and after stay in program order, also where one memory
-// is used with several types (a wave's LDS operations execute in order).
-__device__ inline void lds_order() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // The bounds of a Reach over sorted positions [p0, p1): the packing chunks
 // that overlap them.
 __device__ inline void reach_bounds(const float4* pack, int n_hits, int p0, int p1, Reach& q) {

@@ -388,9 +388,16 @@ __device__ inline uint32_t pack_hist(int parent, uint32_t orig24) {
   return ((uint32_t)parent << 24) | (orig24 == kHoleIdx ? 0xFFFFFFu : orig24);
 }
 
+// LDS accesses before and after stay in program order, also where one memory
+// is used with several types (a wave's LDS operations execute in order).
+__device__ inline void lds_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Per-call preparation of a build in one launch: the first row_blocks blocks
 // write the fine phi index of one (event, layer, z row) each (several where
-// there are more rows than blocks), the blocks after them the packed copy of
+// there are more rows than blocks), or of one per wave (prep_wave_rows), the blocks after them the packed copy of
 // kPackChunk hits each; block 0 also resets the queue head, the per-event
 // counters and the start tick.
 //
@@ -414,9 +421,19 @@ __device__ inline uint32_t pack_hist(int parent, uint32_t orig24) {
 // hit of at most a given chi2 can lie (see Reach).
 constexpr int kPrepThreads = 512;
 constexpr int kPrepKeys = 4096;
+constexpr int kPrepShort = kPrepKeys / (kPrepThreads / 64);
+// Whether a wave takes a row on its own (kPrepShort entries at a time, no
+// barrier): where rows are many and short, a block spends its time at its
+// barriers (108 800 rows of 8 hits and 64 sub-bins: 313 us a block, 141 a wave,
+// 189 before; 435 200 rows of 9 sub-bins: 875, 202, 236; 4 033 sub-bins: 622,
+// 487, 1 939); rows of many hits, or too few to fill the chip with waves, take a
+// block (816 rows of 1 500 hits: 130 us, 175 a wave).
+__host__ __device__ constexpr bool prep_wave_rows(int64_t n_rows, int n_hits, int nf) {
+  return nf < kPrepKeys && n_rows >= 4096 && n_hits <= 64 * n_rows;
+}
 constexpr int kPackChunk = 2048;
 __global__ void __launch_bounds__(kPrepThreads)
-    prep_kernel(int row_blocks, int n_rows, int n_hits, int n_phi, int n_z, int nf, const int32_t* __restrict__ offsets,
+    prep_kernel(int row_blocks, int wave_rows, int n_rows, int n_hits, int n_phi, int n_z, int nf, const int32_t* __restrict__ offsets,
                 const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
                 const float* __restrict__ phi, const float* __restrict__ cov, const int32_t* __restrict__ orig,
                 int32_t* __restrict__ fine, float4* __restrict__ pack, int32_t* __restrict__ queue,
@@ -489,6 +506,36 @@ __global__ void __launch_bounds__(kPrepThreads)
     for (int e = t; e < n_events; e += kPrepThreads) event_done[e] = 0;
   }
   const float inv = fine_inv(nf);
+  if (wave_rows) {  // a row per wave, passes of kPrepShort entries, no barrier
+    int32_t* wc = cnt + wave * kPrepShort;
+    for (int64_t row = (int64_t)blockIdx.x * W + wave; row < n_rows; row += (int64_t)row_blocks * W) {
+      const int el = (int)row / n_z, iz = (int)row - el * n_z;
+      const int32_t* off = offsets + (size_t)el * ((size_t)n_phi * n_z + 1);
+      const int rs = off[iz * n_phi], re = off[(iz + 1) * n_phi];
+      int32_t* f = fine + (size_t)row * (nf + 1);
+      int first = rs;
+      for (int kb = 0; kb <= nf; kb += kPrepShort) {
+        const int m = nf + 1 - kb < kPrepShort ? nf + 1 - kb : kPrepShort;
+        for (int j = lane; j < m; j += 64) wc[j] = 0;
+        lds_order();
+        for (int p = first + lane; p < re; p += 64) {
+          const int k = fine_key(phi[p], inv, nf) - kb;
+          if (k >= m) break;
+          if (k >= 0) atomicAdd(&wc[k], 1);
+        }
+        lds_order();
+        int run = first, total = 0;
+        for (int j = lane; j - lane < m; j += 64) {
+          const int ex = wave_excl_scan(j < m ? wc[j] : 0, lane, total);
+          if (j < m) f[kb + j] = run + ex;
+          run += total;
+        }
+        first = run;
+        lds_order();
+      }
+    }
+    return;
+  }
   for (int row = blockIdx.x; row < n_rows; row += row_blocks) {
     const int el = row / n_z, iz = row - el * n_z;
     const int32_t* off = offsets + (size_t)el * ((size_t)n_phi * n_z + 1);
@@ -541,9 +588,12 @@ int launch_prep(const kf_hits* h, int refine, const int32_t* fine, const float4*
                 int32_t* event_done, int64_t* start_tick, hipStream_t s) {
   const int n_rows = h->n_events * h->n_layers * h->n_z;
   const int n_pack = (int)(((int64_t)h->n_hits + kPackChunk - 1) / kPackChunk);
-  const int row_blocks = n_rows < (1 << 20) ? n_rows : 1 << 20;  // (the grid stays below 2^32 threads)
-  hipLaunchKernelGGL(prep_kernel, dim3(row_blocks + n_pack), dim3(kPrepThreads), 0, s, row_blocks, n_rows, h->n_hits,
-                     h->n_phi, h->n_z, h->n_phi * refine, h->offsets, h->x, h->y, h->z, h->phi, h->cov, h->orig,
+  const int nf = h->n_phi * refine, wave_rows = prep_wave_rows(n_rows, h->n_hits, nf) ? 1 : 0;
+  const int rows = wave_rows ? kPrepThreads / 64 : 1;  // of a block
+  const int64_t want = ((int64_t)n_rows + rows - 1) / rows;
+  const int row_blocks = (int)(want < (1 << 20) ? want : 1 << 20);  // (the grid stays below 2^32 threads)
+  hipLaunchKernelGGL(prep_kernel, dim3(row_blocks + n_pack), dim3(kPrepThreads), 0, s, row_blocks, wave_rows, n_rows,
+                     h->n_hits, h->n_phi, h->n_z, nf, h->offsets, h->x, h->y, h->z, h->phi, h->cov, h->orig,
                      (int32_t*)fine, (float4*)pack, queue, event_done, h->n_events, start_tick);
   return kf_check_launch();
 }
