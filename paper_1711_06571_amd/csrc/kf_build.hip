@@ -190,15 +190,28 @@ __device__ inline void pool_cut(const BuildArgs& A, const Pool& po, const Group&
   }
 }
 
-// A candidate is wide when its window may hold more than kWidePairs pairs;
-// it then first searches where its kProbeHits best hits should lie.
+// A candidate is wide when its window may hold more pairs than kWidePairs and
+// kWideRow for each row of its bounded search, whose four intervals a row are
+// an iteration each, however few hits they hold; it then first searches
+// where its kProbeHits best hits should lie.
+// Measured (us; the macros allow a rebuild to compare):
+//                                 row 0   16   32  512 | probe 8   16   32
+//   400 events of 100, 8 x 64 bins 1224  607  528  528 |     596  607  559
+//   20 events of 20 000, FP64      4781 4787 4778 5281 |    4705 4787 4932
+//   one event of 20 000, FP32       454  451  452  613 |     417  451  504
+//   its windows 1 x 3 cm at least  2078 2093 2175 3581 |    1975 2093 2282
+// kWidePairs of 96, 192, 384: 1 913, 2 093, 2 547 us with the 1 x 3 cm windows, 488,
+// 437, 360 with 400 events of 100 tracks in 63 x 16 bins, the others within 1 %.
 #ifndef KF_WIDE_PAIRS
 #define KF_WIDE_PAIRS 192
 #endif
-#ifndef KF_PROBE_HITS
-#define KF_PROBE_HITS 16
+#ifndef KF_WIDE_ROW
+#define KF_WIDE_ROW 32
 #endif
-constexpr float kWidePairs = KF_WIDE_PAIRS, kProbeHits = KF_PROBE_HITS;
+#ifndef KF_PROBE_HITS
+#define KF_PROBE_HITS 8
+#endif
+constexpr float kWidePairs = KF_WIDE_PAIRS, kWideRow = KF_WIDE_ROW, kProbeHits = KF_PROBE_HITS;
 
 // Hit search of every candidate of the wave, shared by all 64 lanes.
 //
@@ -354,12 +367,18 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
             const float s00 = fabsf(suu) + rq.lam(), s11 = sww + rq.vzz();
             const float s2 = fmaxf(s00 * s11 - suw * suw, 1e-6f * s00 * s11);
             const bool none = rq.none(suu, suw, sww);
-            if (!none) c2b = fminf(kProbeHits * area / (3.1415927f * k_sqrt(s2) * (float)c0), chi2_cut);
-            rq.set(c2b, suu, suw, sww);
-            rw = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
-            if (none) rw.hi = rw.lo - 1;
-            sh = 2;
-            R = rw.n() << sh;
+            const float c2p =
+                none ? chi2_cut : fminf(kProbeHits * area / (3.1415927f * k_sqrt(s2) * (float)c0), chi2_cut);
+            rq.set(c2p, suu, suw, sww);
+            Rows rb = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
+            if (none) rb.hi = rb.lo - 1;
+            wide = (float)c0 * (float)rw.n() > kWidePairs + kWideRow * (float)rb.n();
+            if (wide) {
+              c2b = c2p;
+              rw = rb;
+              sh = 2;
+              R = rw.n() << sh;
+            }
           }
         }
         again = __any(wide && c2b < chi2_cut);
