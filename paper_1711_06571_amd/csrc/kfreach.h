@@ -14,8 +14,10 @@ KFR float bits_f(uint32_t u) { return __builtin_bit_cast(float, u); }
 KFR uint32_t f_bits(float f) { return __builtin_bit_cast(uint32_t, f); }
 
 constexpr float kTwoPiF = 6.283185307179586f;
-// Margins of a window's stored-value intervals (rad, cm).
-constexpr float kEpsPhi = 1e-5f, kEpsZ = 1e-4f;
+// Margins of a window's stored-value intervals (rad, cm), and of the z rows'
+// edges by the barrel's half-length: the edges and a position's row are formed
+// in FP32 from up to twice that (some 4 roundings of 6e-8).
+constexpr float kEpsPhi = 1e-5f, kEpsZ = 1e-4f, kEpsRow = 5e-7f;
 
 // z rows lo..hi a window overlaps, and the row of its middle; at(i) counts
 // them from the middle row on.
@@ -29,7 +31,8 @@ KFR int row_of(float v, float zh, int nz) {
   return i < 0 ? 0 : (i > nz - 1 ? nz - 1 : i);
 }
 KFR Rows rows_of(float z, float dz, float zh, int nz) {
-  const int lo = row_of(z - dz, zh, nz), hi = row_of(z + dz, zh, nz), m = row_of(z, zh, nz);
+  const float e = dz + kEpsRow * zh;
+  const int lo = row_of(z - e, zh, nz), hi = row_of(z + e, zh, nz), m = row_of(z, zh, nz);
   return {lo, hi, m < lo ? lo : (m > hi ? hi : m)};
 }
 
@@ -115,8 +118,9 @@ KFR void reach_arcs(const Reach& q, float suu, float suw, float sww, float rc, f
   lo[0] = lo[1] = 1.f;
   hi[0] = hi[1] = 0.f;
   // residuals in z of the row's hits (the end rows hold all hits beyond)
-  float l1 = row == 0 ? -zm : (float)row * rh - zh - z - kEpsZ;
-  float h1 = row == nz - 1 ? zm : (float)(row + 1) * rh - zh - z + kEpsZ;
+  const float er = kEpsZ + kEpsRow * zh;
+  float l1 = row == 0 ? -zm : (float)row * rh - zh - z - er;
+  float h1 = row == nz - 1 ? zm : (float)(row + 1) * rh - zh - z + er;
   l1 = l1 < -zm ? -zm : l1;
   h1 = h1 > zm ? zm : h1;
   if (!(zm < 1e9f)) {  // (nothing to gain, and the squares below stay finite)
