@@ -259,11 +259,10 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
                                  unsigned& tested) {
   static_assert(NPT >= 1 && NPT <= NP, "pairs per lane");
   const int nz = A.n_z, nf = A.n_phi * A.refine;
-  const float inv = fine_inv(nf);
   // this lane's window as conservative stored-value intervals (the exact
-  // test decides): a half-width hw about phip (3.14159 and more: the whole
+  // test decides): a half-width half() about phip (3.14159 and more: the whole
   // circle), z rows taken from the middle one outwards
-  float phip = 0.f, hw = 0.f;
+  float phip = 0.f;
   Rows rw = {0, -1, 0};
   // Per candidate, what every hit test shares: for dphi < pi/2 the angle
   // test |atan2(cross, dot)| <= dphi is dot > 0 and |cross| <= tan(dphi) dot
@@ -272,6 +271,7 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
   // H P H^T of the prediction.
   float fx = 0.f, fy = 0.f, fz = 0.f, fdz = 0.f, fdphi = 0.f, ftan = 0.f;
   float firr = 0.f, suu = 0.f, suw = 0.f, sww = 0.f;
+  auto half = [&]() { return fdphi + kEpsPhi; };
   if (pok) {
     fx = (float)Xp[0];
     fy = (float)Xp[1];
@@ -279,8 +279,7 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
     fdz = (float)dz_w;
     fdphi = (float)dphi_w;
     phip = wrap_2pi(atan2f(fy, fx));
-    hw = fdphi + kEpsPhi;
-    rw = rows_of(fz, fdz + kEpsZ, A.z_half, ku64<T>(A.n_z));
+    rw = rows_of(fz, fdz + kEpsZ, ku64<T>(A.z_half), ku64<T>(A.n_z));
     // (the angle test runs in FP32: so does the tangent of its bound)
     ftan = !(dphi_w < T(1.5707963267948966)) ? -1.f : tanf((float)dphi_w);
     const T rr = k_sqrt(Xp[0] * Xp[0] + Xp[1] * Xp[1]);
@@ -296,7 +295,7 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
   // where the window wraps at 2 pi, four of a Reach)
   Reach rq = {0.f, 0.f, 0u, 0u};
   float al[2] = {1.f, 1.f}, ah[2] = {0.f, 0.f};  // the row's arcs
-  int sh = phi_parts(phip, hw);
+  int sh = phi_parts(phip, half());
   int R = pok ? rw.n() << sh : 0;
   const float chi2_cut = A.chi2_cut;
   float thr = __builtin_inff();  // chi2 of a hit that may enter the pool
@@ -315,13 +314,16 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
     q3 = 0;
     const int r = sh == 0 ? 2 * it : it;
     if (r < R) {
+      const int nf = ku64<T>(A.n_phi) * ku64<T>(A.refine), nz = ku64<T>(A.n_z);
+      const float inv = fine_inv(nf);
       const int row = rw.at(r >> sh), i = r & ((1 << sh) - 1);
       if (sh == 2) {
         if (i == 0)
-          reach_arcs(rq, suu, suw, sww, k_sqrt(fx * fx + fy * fy), fz, hw, fdz + kEpsZ, row, nz, A.z_half, al, ah);
+          reach_arcs(rq, suu, suw, sww, k_sqrt(fx * fx + fy * fy), fz, half(), fdz + kEpsZ, row, nz,
+                     ku64<T>(A.z_half), al, ah);
         arc_part(phip, i & 2 ? al[1] : al[0], i & 2 ? ah[1] : ah[0], i & 1, a, b);
       } else {
-        phi_part(phip, hw, i, a, b);
+        phi_part(phip, half(), i, a, b);
       }
       if (a <= b) {
         const int32_t* f = frow + (size_t)row * (nf + 1);
@@ -343,7 +345,6 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
   float an = 1.f, bn = 0.f;
   int p0n = 0, p1n = 0, p2n = 0, p3n = 0;
   bool wide = false, pruned = false;
-  float c2b = chi2_cut;
   bool look = A.counters == nullptr;  // wide windows still to be looked for
   bool again = false;                 // a wide candidate's bound still to be checked
   int Rmax = wave_max(iters());
@@ -363,25 +364,24 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
           reach_bounds(A.hpack, A.n_hits, of[rw.lo * A.n_phi], of[(rw.hi + 1) * A.n_phi], rq);
           wide = rq.usable(suu, sww);
           if (wide) {
-            const float area = 4.f * fminf(hw, 3.1415927f) * k_sqrt(fx * fx + fy * fy) * A.z_half / (float)nz;
+            const float area = 4.f * fminf(half(), 3.1415927f) * k_sqrt(fx * fx + fy * fy) * A.z_half / (float)nz;
             const float s00 = fabsf(suu) + rq.lam(), s11 = sww + rq.vzz();
             const float s2 = fmaxf(s00 * s11 - suw * suw, 1e-6f * s00 * s11);
             const bool none = rq.none(suu, suw, sww);
             const float c2p =
                 none ? chi2_cut : fminf(kProbeHits * area / (3.1415927f * k_sqrt(s2) * (float)c0), chi2_cut);
             rq.set(c2p, suu, suw, sww);
-            Rows rb = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
+            Rows rb = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), ku64<T>(A.z_half), nz);
             if (none) rb.hi = rb.lo - 1;
             wide = (float)c0 * (float)rw.n() > kWidePairs + kWideRow * (float)rb.n();
             if (wide) {
-              c2b = c2p;
               rw = rb;
               sh = 2;
               R = rw.n() << sh;
             }
           }
         }
-        again = __any(wide && c2b < chi2_cut);
+        again = __any(wide && rq.c2 < chi2_cut);
         Rmax = wave_max(iters());
         continue;
       }
@@ -535,7 +535,7 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
     if (!again) break;
     // the bounds of the wide candidates
     again = false;
-    unsigned long long wm = __ballot(wide && c2b < chi2_cut);
+    unsigned long long wm = __ballot(wide && rq.c2 < chi2_cut);
     unsigned long long redo = 0ull;  // lanes of the seeds to be searched again
     const unsigned long long gm = ((1ull << gr.S) - 1ull);
     while (wm) {
@@ -545,10 +545,10 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
       pool_cut<T>(A, po, gr, s, lane, chi2, nhits, e0, thr, cut);
       lim = true;
       bool miss = false;
-      if (gr.sidx == s && wide && c2b < chi2_cut) {
+      if (gr.sidx == s && wide && rq.c2 < chi2_cut) {
         pruned = cut && thr < chi2_cut && (po.seen[lane] != 0 || hole_ok);
-        miss = !pruned || thr > c2b;
-        if (miss) c2b = pruned ? thr : chi2_cut;
+        miss = !pruned || thr > rq.c2;
+        if (miss) rq.c2 = pruned ? thr : chi2_cut;
       }
       if (__any(miss)) redo |= sm;
     }
@@ -559,8 +559,8 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
       if (gr.slot == 0) po.cnt[gr.sidx] = 0;
       if (!pruned) po.seen[lane] = 0;
       if (wide && R0 > 0) {
-        rq.set(c2b, suu, suw, sww);
-        rw = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), A.z_half, nz);
+        rq.set(rq.c2, suu, suw, sww);
+        rw = rows_of(fz, fminf(fdz + kEpsZ, rq.dz(sww)), ku64<T>(A.z_half), nz);
       }
       R = pok ? rw.n() << sh : 0;
     }
