@@ -200,7 +200,7 @@ typedef struct {
   int32_t first_layer; /* first layer searched; seeds sit on first_layer - 1 */
   int32_t window_mode; /* 0 plain; 1 learned (mlp must point to a network block) */
   const void* mlp;     /* device pointer to the window network block (kf_mlp_block_bytes) */
-  int32_t lanes_per_block; /* 64, 128, 256 (0: the widest whose LDS fits) */
+  int32_t lanes_per_block; /* 64, 128, 256 (0: kf_build, with which a CU holds the most waves; kf_build_det, the widest whose LDS fits) */
   int32_t persistent_blocks; /* blocks of the persistent grid (0: CUs x resident blocks per CU) */
   int32_t arith;       /* KF_ARITH_F32 or KF_ARITH_F64 */
   int32_t phi_refine;  /* sub-bins per phi bin of the fine index the hit search uses, 1..64 (0: 64) */

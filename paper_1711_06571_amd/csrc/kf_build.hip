@@ -130,7 +130,7 @@ constexpr uint32_t kNoHit = 0xFFFFFFu;  // the position of a hole
 struct Pool {
   uint2* e;
   int32_t* cnt;
-  int32_t* seen;
+  uint8_t* seen;
   int stride, full;
 };
 
@@ -255,7 +255,7 @@ constexpr float kWidePairs = KF_WIDE_PAIRS, kWideRow = KF_WIDE_ROW, kProbeHits =
 template <typename T, int NPT>
 __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool pok, const T Xp[6], const T Pp[21],
                                  T dphi_w, T dz_w, T chi2, int nhits, bool hole_ok, const Group& gr, const Pool& po,
-                                 int32_t* start, int lane, bool& seen, bool& cut, unsigned& scanned,
+                                 int8_t* start, int lane, bool& seen, bool& cut, unsigned& scanned,
                                  unsigned& tested) {
   static_assert(NPT >= 1 && NPT <= NP, "pairs per lane");
   const int nz = A.n_z, nf = A.n_phi * A.refine;
@@ -402,7 +402,7 @@ __device__ inline void coop_scan(const BuildArgs& A, int ev, int e0, int l, bool
       // its slot in its half, else the one whose pairs run on from before
 #pragma unroll
       for (int h = 0; h < NPT; ++h) start[h * 64 + lane] = -1;
-      if (all > 0 && off >= base && off - base < 64 * NPT) start[off - base] = lane;
+      if (all > 0 && off >= base && off - base < 64 * NPT) start[off - base] = (int8_t)lane;
       lds_order();
       int c[NPT], p[NPT];
       bool valid[NPT];
@@ -745,11 +745,11 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
   uint16_t* mlp_buf = (uint16_t*)wave_tl;
   Pool po;
   po.e = (uint2*)wave_tl;
-  po.cnt = (int32_t*)(base + lp.pub) + (size_t)wave * 128;
-  po.seen = po.cnt + 64;
+  po.cnt = (int32_t*)(base + lp.pub + (size_t)wave * pub_bytes(S));
+  po.seen = (uint8_t*)(po.cnt + SEEDS);
   po.stride = (kPoolPerCap + 1) * S;
   po.full = kPoolPerCap * S;
-  int32_t* start = (int32_t*)(base + lp.acc) + (size_t)wave * 64 * NP;
+  int8_t* start = (int8_t*)(base + lp.acc) + (size_t)wave * 64 * NP;
   (void)mlp_buf;
   const int sidx = lane / S, slot = lane - (lane / S) * S, sbase = sidx * S;
   const bool lane_used = sidx < SEEDS;
@@ -1077,9 +1077,9 @@ int launch(const BuildArgs& A, int lanes, int blocks, int hist_waves, hipStream_
   if (kf_check(hipGetDevice(&dev))) return KF_E_HIP;
   if (kf_check(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev))) return KF_E_HIP;
   auto plan = [&](int ln) { return lds_plan(LB, ln / 64, A.cap, (int)sizeof(T), LEARNED, HYB).total; };
-  if (lanes == 0) {  // automatic: the widest block whose LDS fits
-    lanes = 256;
-    while (lanes > 64 && plan(lanes) > (size_t)max_lds) lanes /= 2;
+  if (lanes == 0) {  // automatic
+    lanes = plan_lanes(LB, A.cap, (int)sizeof(T), LEARNED, HYB, (size_t)max_lds);
+    if (lanes == 0) return KF_E_UNSUPPORTED;
   }
   const int nwaves = lanes / 64;
   const size_t lds = plan(lanes);
