@@ -278,19 +278,24 @@ int fit_launch(const kf_geometry* g, int32_t n, int32_t ld, int32_t first_layer,
   if (!hits || !seed_par || !seed_cov || !q || !out_par || !out_cov || !out_chi2 || !out_ndof || !out_status)
     return KF_E_INVALID_ARG;
   const int bs = 256;
-  // Loading ahead pays where many waves share the memory (14 layers, FP64: 10 000
-  // tracks 39.3 -> 37.2 us, 1 M 414 -> 400; FP32 3 to 8 %); with few, the
-  // loads are short and the moves cost more (1 000 tracks: 35.7 -> 36.1 us,
-  // hybrid 49.4 -> 51.5).
-  const bool ahead = n >= 8192;
-  if (arith == KF_ARITH_F64)
-    hipLaunchKernelGGL((ahead ? fit_kernel<double, HYB, true> : fit_kernel<double, HYB, false>), dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g),
-                       n, ld, first_layer, hits, hole_mask, seed_par, seed_cov, q, out_par, out_cov, out_chi2,
-                       out_ndof, out_status);
+  // Loading ahead pays where many waves share the memory, the later the longer
+  // the chain that the loads would wait for; with few waves the loads are short
+  // and the moves cost more.  By hits fitted, the line where both forms take
+  // the same (one side of it, then the other, us without and with; 7 and 14
+  // layers): FP32 16 384 x 7 19.3 to 19.5, 10 000 x 14 37.1 to 35.4; FP64 20 000 x 7
+  // 23.7 to 24.0, 20 000 x 14 44.5 to 43.5; hybrid FP32 40 000 x 7 24.9 to 25.2, 40 000
+  // x 14 48.6 to 46.1; hybrid FP64 65 536 x 7 34.2 to 35.2, 65 536 x 14 66.5 to 64.5.
+  const bool f64 = arith == KF_ARITH_F64;
+  const int64_t line = HYB ? (f64 ? 900000 : 440000) : (f64 ? 280000 : 140000);
+  const bool ahead = (int64_t)n * (g->n_layers - first_layer) >= line;
+  if (f64)
+    hipLaunchKernelGGL((ahead ? fit_kernel<double, HYB, true> : fit_kernel<double, HYB, false>),
+                       dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g), n, ld, first_layer, hits,
+                       hole_mask, seed_par, seed_cov, q, out_par, out_cov, out_chi2, out_ndof, out_status);
   else
-    hipLaunchKernelGGL((ahead ? fit_kernel<float, HYB, true> : fit_kernel<float, HYB, false>), dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g),
-                       n, ld, first_layer, hits, hole_mask, seed_par, seed_cov, q, out_par, out_cov, out_chi2,
-                       out_ndof, out_status);
+    hipLaunchKernelGGL((ahead ? fit_kernel<float, HYB, true> : fit_kernel<float, HYB, false>),
+                       dim3((n + bs - 1) / bs), dim3(bs), 0, (hipStream_t)stream, to_k(g), n, ld, first_layer, hits,
+                       hole_mask, seed_par, seed_cov, q, out_par, out_cov, out_chi2, out_ndof, out_status);
   return kf_check_launch();
 }
 
