@@ -588,6 +588,12 @@ def main():
     n_pred, n_scan, n_chi2, n_upd = [int(v) for v in cnt.cpu().numpy()]
     build_flop = (n_pred * (FLOP_PREDICT + FLOP_WINDOW) + n_scan * FLOP_WINDOW_TEST + n_chi2 * FLOP_CHI2 +
                   n_upd * FLOP_UPDATE)
+    # a build that counts looks at every hit, the timed one passes over hits that
+    # cannot survive: rates of the counted work are over the time of builds that count
+    evc = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
+    step(arith, evc, extra=exc)
+    torch.cuda.synchronize()
+    count_ms = evc[1].elapsed_time(evc[2])
     ndof = fout["ndof"].cpu().numpy()[:n]
     st = fout["status"].cpu().numpy()[:n]
     n_upd_fit = int(ndof.sum() // 2)
@@ -599,11 +605,12 @@ def main():
     peak = PEAK_TFLOPS[args.arith]
     flop_of = {"kf_build": build_flop, "kf_fit": fit_flop}
     if dom in flop_of:
-        ach = flop_of[dom] / (stage_ms[dom] * 1e-3) / 1e12
+        ach_ms = count_ms if dom == "kf_build" else stage_ms[dom]
+        ach = flop_of[dom] / (ach_ms * 1e-3) / 1e12
         kname = f"build_kernel<{'double' if args.arith == 'f64' else 'float'}, false, false>" if dom == "kf_build" else dom
         roof = {"bound": "alu", "achieved": round(ach, 3), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(ach / peak, 4), "traffic": measured_traffic(kname), "kernel": dom,
-                "avg_ms": stage_ms[dom]}
+                "avg_ms": stage_ms[dom], "achieved_over_ms": round(ach_ms, 4)}
     else:
         roof = {"bound": "hbm", "achieved": None, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": None,
                 "traffic": None, "kernel": dom, "avg_ms": stage_ms[dom]}
@@ -625,7 +632,8 @@ def main():
                  "fit_gflop": round(fit_flop / 1e9, 3),
                  "fit_algorithmic_gb": round(n * FIT_BYTES_PER_TRACK / 1e9, 3),
                  "fit_gbs": round(n * FIT_BYTES_PER_TRACK / (stage_ms["kf_fit"] * 1e-3) / 1e9, 1),
-                 "build_tflops": round(build_flop / (stage_ms["kf_build"] * 1e-3) / 1e12, 3),
+                 "build_counted_ms": round(count_ms, 4),
+                 "build_tflops": round(build_flop / (count_ms * 1e-3) / 1e12, 3),
                  "fit_tflops": round(fit_flop / (stage_ms["kf_fit"] * 1e-3) / 1e12, 3)},
         "efficiency_75pct": round(eff, 4),
         "fit_status_ok": round(float(np.mean(st == 0)), 4),
