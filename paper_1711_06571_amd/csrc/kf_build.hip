@@ -86,8 +86,8 @@ struct BuildArgs {
 
 // ku / kv in FP64 builds only: there, kernel arguments and per-seed values
 // that the layer loop uses are recomputed where they are used instead of
-// being hoisted out of the loop and spilled (the FP32 build does not spill;
-// the barriers would only cost it issue slots)
+// being hoisted out of the loop and spilled (the FP32 build spills 28 to 68 B a
+// lane; with them 24 to 32, and its times stay within 1 %)
 template <typename T, typename U> __device__ inline U ku64(U v) {
   if constexpr (sizeof(T) == 8) return ku(v);
   else return v;
@@ -241,7 +241,7 @@ constexpr float kWidePairs = KF_WIDE_PAIRS, kWideRow = KF_WIDE_ROW, kProbeHits =
 // out cannot survive; it would only have been counted, and the counts matter
 // to "any child" (known from the accepted hits or the hole) and to "cut to
 // cap" (known once the seed accepted more than cap).  Work counters ask for
-// every hit: no bound then.  Pairs, same events: 470 M -> 115 M.
+// every hit: no bound then.  Pairs, same events: 462 M -> 123 M.
 //
 // The tests and chi2 run in FP32 in both arithmetic modes, from the
 // prediction rounded to FP32: their rounding (chi2 ~ 3e-5 at the cut,
@@ -694,10 +694,10 @@ __device__ inline int best_children(const BuildArgs& A, const Pool& po, const Gr
 #define KF_BUILD_F64_LEARNED_WAVES 2
 #endif
 
-// Pairs per lane and round: NP in every build.  Learned FP64 builds took
-// one while they spilled around the network (32 events: 17.35 -> 17.28 ms);
-// with their state between layers in LDS two pay (11.45 -> 10.79 ms, hybrid
-// state 11.40 -> 11.04 ms).  The macro allows a rebuild to compare.
+// Pairs per lane and round: NP in every build (learned FP64 builds of 32 events
+// 11.45 ms with one, 10.79 with two, hybrid state 11.40 and 11.04; the plain
+// hybrid FP64 build of 20 events 5.21 and 5.00).  The macro allows a rebuild to
+// compare.
 #ifndef KF_LEARNED_F64_NPT
 #define KF_LEARNED_F64_NPT 2
 #endif
@@ -713,14 +713,14 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? KF_BUILD_F32_WAVES
   extern __shared__ __align__(16) uint32_t lds[];
   const int lane = threadIdx.x & 63;
   // the wave index as a uniform value in FP64 builds: the per-wave addresses
-  // derived from it then stay in scalar registers (the FP32 build, which
-  // does not spill, measured slower with it)
+  // derived from it then stay in scalar registers (the FP32 build measured from
+  // 1 % faster to 2 % slower with it)
   const int wave = sizeof(T) == 8 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
   const int nwaves = blockDim.x >> 6;
   const int LB = A.n_layers - A.first_layer;  // searched layers
   const LdsPlan lp = lds_plan(LB, nwaves, S, (int)sizeof(T), LEARNED, HYB);
   constexpr int NPL = xs_npl((int)sizeof(T), LEARNED, HYB);
-  constexpr bool XS = NPL >= 0;  // state between layers in LDS
+  constexpr bool XS = NPL >= 0;  // xs in LDS
   char* base = (char*)lds;
   // this wave's back-pointer table (written once per new candidate and layer,
   // read once per seed at the end)

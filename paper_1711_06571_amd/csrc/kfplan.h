@@ -12,26 +12,27 @@ constexpr int NP = 2;
 
 // LDS of one block (byte offsets), per wave:
 //   stash    [27][64] f32      each slot's state before this layer's prediction
-//                              (FP64: only the covariance entries not in xs)
+//                              (FP64: its first 21 - NPL values, the rest in
+//                              the first half of xs)
 //   record   [SEEDS][27] f32   best finished candidate of each seed
 //   recfield [SEEDS][5] i32    valid, nhits, status, last layer, slot
 //   starts   [64 NP] i8 run starts of the cooperative hit search
 //   publish  [SEEDS] i32 entries of each seed's pool, [64] u8 whether one of a
 //            candidate's hits was accepted
 //   pool     [8 cap][SEEDS] of 8 B: a seed's accepted hits (chi2, position and
-//            slot), ranked and cut to cap when the next round might not fit
+//            slot), ranked and cut to cap when an insertion finds it full, and
+//            room for the holes of its candidates
 //   mlp      activation buffer of the learned window (the network runs before
 //            the hit search, so the pools of a learned build live in it)
-//   xs       [6 + NPL][64] f64 FP64 builds: the state between layers (below)
-// FP64 builds keep each candidate's state between layers in LDS as
-// doubles: the position and momentum and the last NPL covariance entries
-// (the rest of the covariance stays in registers, its FP32 copy in the
-// stash for the finished record).  Held in registers through the layer
-// loop, these values were spilled to scratch memory and reloaded at every
-// layer; the stash then needs only the covariance entries not held in LDS.
-// NPL: what fits two blocks of four waves per CU (the learned builds' network
-// buffers leave room for 2; the hybrid state, which spills more, takes all
-// it can), 12 in the Cartesian state (measured best).
+//   xs       [6 + NPL][64] f64 FP64 builds: the rest of the state before the
+//            prediction (FP32, first half), the last (6 + NPL) / 2 covariance
+//            entries of the prediction during the hit search (second half)
+// The state between layers stays in registers; what does not fit there is
+// spilled (FP64: 280 B a lane, hybrid state 344, FP32 at most 68).  The children's
+// keys take the stash or the first half of xs once the records are written.
+// NPL: what fits two blocks of four waves per CU at cap 6 with the learned
+// builds' network buffers (2) and in the hybrid state (20; 18 and 16 measured
+// 0.7 and 1 % slower), 12 in the Cartesian state (14: 0.8 % slower).
 __host__ __device__ constexpr int xs_npl(int tsize, bool learned, bool hyb) {
   return tsize == 8 ? (learned ? 2 : hyb ? 20 : 12) : -6;
 }
