@@ -176,14 +176,15 @@ size_t hit_bin_workspace_bytes(int32_t n_events, int32_t n_layers, int32_t n_phi
  * left out of every bin and counted in *out_bad (int32, may be NULL); the
  * sorted arrays then hold n_hits - bad hits and their tail is unspecified.
  * Any input order is accepted.  When every event's hits come grouped by
- * layer in ascending order, all valid, n_phi * n_z <= 4096, and the (event,
- * layer) ranges are many (one for every second compute unit) or the mean bin
- * is large, blocks that each sort a range, or a part of one, sort the call;
- * otherwise the general kernels do, with the same result.  The environment
- * variable KFTRACK_HIT_BIN_PATH=grouped (try the grouped path whatever the
- * number of ranges) or =general overrides the choice.  Diagnostic: after the
- * call, the int32 at byte offset hit_bin_workspace_bytes(...) - 256 of ws is 0
- * when the grouped path sorted the call and 1 otherwise.
+ * layer in ascending order, all valid, n_phi * n_z <= 4096, and the call is not
+ * among the smallest, blocks that each sort an (event, layer) range, or a part
+ * of one, sort the call; otherwise the general kernels do, with the same
+ * result.  The environment variable KFTRACK_HIT_BIN_PATH=grouped (try the
+ * grouped path whatever the size) or =general overrides the choice.
+ * Diagnostics, after the call, int32 words of ws: at byte offset
+ * hit_bin_workspace_bytes(...) - 252, the path that sorted the call (0 grouped,
+ * 1 general); at - 256, 0 where the grouped path sorted a call of at least six
+ * ranges per compute unit or one under =grouped, and 1 otherwise.
  */
 int hit_bin(const kf_geometry* g, int32_t n_events, const int32_t* event_offsets, int32_t n_phi, int32_t n_z,
             int32_t n_hits, const int32_t* layer, const float* xyz, const float* cov, int32_t* offsets,

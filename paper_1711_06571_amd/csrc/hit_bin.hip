@@ -31,8 +31,8 @@ constexpr int kWideGrid = 2048;   // blocks of the grid-stride kernels: eight pe
 __global__ void clear_kernel(int32_t* __restrict__ count, int64_t n, int32_t* __restrict__ ctl,
                              int32_t* __restrict__ bad) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctl[0] = 1;
-    ctl[1] = 0;
+    ctl[0] = ctl[1] = 1;
+    ctl[2] = 0;
     if (bad) *bad = 0;
   }
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -83,14 +83,17 @@ __device__ inline bool finite3(float x, float y, float z) {
 // ---- Bins and angles ---------------------------------------------------------
 //
 // Every hit's bin ((event * L + layer) * nb + bin) * F + the piece of the bin
-// its angle lies in, -1 for a hit on a layer
-// outside [0, L) or with a non-finite coordinate, and its angle.  Where the
-// grouped path is tried, the first hit of every (event, layer) range and,
-// per block, whether its hits kept the order that path needs; otherwise the
-// general path's counts and the arrival index among the bin's hits (the value
-// the count's atomic returns; the rank pass fixes the order).  The pass also
-// clears what the kernels after it raise.  FP64 arithmetic bounds it (an
-// arctangent and two quotients a hit): 8.16 M hits in 109 us, 24 B a hit.
+// its angle lies in, -1 for a hit on a layer outside [0, L) or with a
+// non-finite coordinate, and its angle.  Where the grouped path is tried, the
+// first hit of every (event, layer) range and, per block, whether its hits kept
+// the order that path needs; otherwise the general path's counts and the
+// arrival index among the bin's hits (the value the count's atomic returns; the
+// rank pass fixes the order).  Blocks whose first hits are plainly not in order
+// leave theirs to count_kernel, which bins and counts them in one pass, the
+// atomics behind the arithmetic (8 events of 50 000 tracks in any order: 1.93 ms
+// for the call with a pass for the counts alone, 1.70 without the attempt).
+// The pass also clears what the kernels after it raise.  FP64 arithmetic bounds
+// it (an arctangent and two quotients a hit): 8.16 M hits in 109 us, 24 B a hit.
 constexpr int kBinGrid = 2048;
 
 struct BinArgs {
@@ -105,34 +108,28 @@ struct BinArgs {
   int64_t NB;
   int32_t F;
   int32_t* seg;      // [E L + 1] first hit of every range
-  uint8_t* blk_bad;  // [kBinGrid] 1: the block's hits are not grouped or not all valid, or its events do not tile the hits
+  // [kBinGrid] bit 0: the block's hits are not grouped or not all valid, or its
+  // events do not tile the hits; bit 1: its hits are left to count_kernel
+  uint8_t* blk_bad;
   int32_t* ctl;      // see BinWs
   int32_t* bad;      // may be null
-  int32_t try_grouped;
+  int32_t flag0, try_grouped;
 };
 
-__global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
-  const int n = A.n, E = A.E, L = A.L, nb = A.n_phi * A.n_z, EL = E * L;
-  const int t = threadIdx.x;
-  bool ok = true;
-  if (A.try_grouped) {
-    if (blockIdx.x == 0 && t == 0) {
-      A.ctl[0] = 0;
-      A.ctl[1] = 0;
-      if (A.bad) *A.bad = 0;
-    }
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + t; k < A.NB; k += (int64_t)gridDim.x * blockDim.x)
-      A.count[k] = 0;
-    if (n == 0)
-      for (int k = blockIdx.x * blockDim.x + t; k <= EL; k += gridDim.x * blockDim.x) A.seg[k] = 0;
-    if (A.eoff)
-      for (int64_t e = blockIdx.x * (int64_t)blockDim.x + t; e < E; e += (int64_t)gridDim.x * blockDim.x)
-        ok = ok && tiles(A.eoff, E, n, (int)e);
-  }
-  // a run of hits per block, so most hits need no search for their event
+// The hits [i0, i1) of this block: consecutive, so most need no search for
+// their event, and a multiple of its threads.
+__device__ inline void run_of_block(int n, int& i0, int& i1) {
   const int per = (int)((((int64_t)n + gridDim.x - 1) / gridDim.x + 255) & ~(int64_t)255);
-  const int64_t i0w = (int64_t)blockIdx.x * per;
-  const int i0 = i0w < n ? (int)i0w : n, i1 = i0w + per < n ? (int)(i0w + per) : n;
+  const int64_t at = (int64_t)blockIdx.x * per;
+  i0 = at < n ? (int)at : n;
+  i1 = at + per < n ? (int)(at + per) : n;
+}
+
+// Bins the block's hits, and counts them (COUNT) or writes the range starts and
+// returns whether they are in order.
+template <bool COUNT>
+__device__ inline bool bin_run(const BinArgs& A, const RowGeom& rg, int i0, int i1) {
+  const int n = A.n, E = A.E, L = A.L, nb = A.n_phi * A.n_z, t = threadIdx.x;
   const int32_t* eoff = A.eoff;
   int elo = 0, ehi = 1;
   if (eoff && i0 < i1) {
@@ -140,13 +137,14 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
     ehi = event_of(eoff, elo, E, i1 - 1) + 1;
   }
   const double turns = A.n_phi / kTwoPi;
+  bool ok = true;
   int ln = 0, lpn = -1;
   float xn = 0.f, yn = 0.f, zn = 0.f;
   auto load = [&](int k) {
     if (k >= i1 - i0) return;
     const int i = i0 + k;
     ln = A.layer[i];
-    lpn = i > 0 ? A.layer[i - 1] : -1;
+    if (!COUNT) lpn = i > 0 ? A.layer[i - 1] : -1;
     xn = A.xyz[i];
     yn = A.xyz[(size_t)n + i];
     zn = A.xyz[2 * (size_t)n + i];
@@ -160,7 +158,7 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
     const int e = eoff ? event_of(eoff, elo, ehi, i) : 0;
     if (l < 0 || l >= L || !finite3(xf, yf, zf)) {
       A.gbin_of[i] = -1;
-      if (!A.try_grouped && A.bad) atomicAdd(A.bad, 1);
+      if (COUNT && A.bad) atomicAdd(A.bad, 1);
       ok = false;
       continue;
     }
@@ -173,16 +171,43 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
     const int pc = (int)(((double)phf * turns - (double)ip) * A.F);
     A.gbin_of[i] = gb * A.F + (pc < 0 ? 0 : (pc < A.F ? pc : A.F - 1));
     A.phi_of[i] = phf;
-    if (!A.try_grouped) {
-      A.arrival[i] = atomicAdd(&A.count[gb], 1);
-      continue;
-    }
-    ok = range_starts(eoff, E, L, n, i, e, l, lp, A.seg) && ok;
+    if (COUNT) A.arrival[i] = atomicAdd(&A.count[gb], 1);
+    else ok = range_starts(eoff, E, L, n, i, e, l, lp, A.seg) && ok;
   }
-  if (A.try_grouped) {
-    const int all_ok = __syncthreads_and(ok);
-    if (t == 0) A.blk_bad[blockIdx.x] = all_ok ? 0 : 1;
+  return ok;
+}
+
+__global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
+  const int n = A.n, E = A.E, EL = E * A.L, t = threadIdx.x;
+  int i0, i1;
+  run_of_block(n, i0, i1);
+  if (!A.try_grouped) {
+    (void)bin_run<true>(A, rg, i0, i1);
+    return;
   }
+  // (a descent of the layer starts an event in ordered input; loaded first, the
+  // clearing below hides it)
+  const bool falls = t > 0 && t < i1 - i0 && A.layer[i0 + t] < A.layer[i0 + t - 1];
+  if (blockIdx.x == 0 && t == 0) {
+    A.ctl[0] = A.flag0;
+    A.ctl[1] = 0;
+    A.ctl[2] = 0;
+    if (A.bad) *A.bad = 0;
+  }
+  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + t; k < A.NB; k += (int64_t)gridDim.x * blockDim.x) A.count[k] = 0;
+  if (n == 0)
+    for (int k = blockIdx.x * blockDim.x + t; k <= EL; k += gridDim.x * blockDim.x) A.seg[k] = 0;
+  if (__syncthreads_count(falls) > 64) {
+    if (t == 0) A.blk_bad[blockIdx.x] = 3;
+    return;
+  }
+  bool ok = true;
+  if (A.eoff)
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + t; e < E; e += (int64_t)gridDim.x * blockDim.x)
+      ok = ok && tiles(A.eoff, E, n, (int)e);
+  ok = bin_run<false>(A, rg, i0, i1) && ok;
+  const int all_ok = __syncthreads_and(ok);
+  if (t == 0) A.blk_bad[blockIdx.x] = all_ok ? 0 : 1;
 }
 
 // ---- Grouped path -----------------------------------------------------------
@@ -221,6 +246,7 @@ constexpr int kSegMinPart = 1024;
 // of 1 500: 100 and 79, of 3 000: 134 and 203).
 constexpr int kSegSmall = 2000;
 constexpr int kSegSmallPart = 1664;
+constexpr int kSegMinCall = 64000;                // hits and a quarter of the bins of a call that tries the path
 constexpr int kSegMaxBins = 4096;                // n_phi * n_z the grouped path takes: 12 bits
 constexpr int kSegIdxBits = 20;                  // an index inside the range beside the bin
 // Parts of a range up to which each stages the whole range; with more, a part
@@ -282,7 +308,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
   for (int k = t; k < (A.n_blk + 3) / 4; k += kSegThreads) {
     const int left = A.n_blk - 4 * k;
     const uint32_t w = ((const uint32_t*)A.blk_bad)[k];
-    bad = bad || (left >= 4 ? w : w & ((1u << (8 * left)) - 1)) != 0;
+    bad = bad || ((left >= 4 ? w : w & ((1u << (8 * left)) - 1)) & 0x01010101u) != 0;
   }
   if (t >= kSegThreads - 64) {
     const int r = range_of_block(A.seg, EL, A.part, b, lane);
@@ -291,7 +317,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
   for (int k = t; k <= np; k += kSegThreads) start[k] = 0;
   // (without a bad block every entry of seg is written, ascending in [0, n])
   if (__syncthreads_or(bad)) {
-    if (t == 0) A.ctl[0] = 1;
+    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
     return;
   }
   const int sg = s_sg;
@@ -304,7 +330,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
     return;
   }
   if (len >= 1 << kSegIdxBits) {
-    if (t == 0) A.ctl[0] = 1;
+    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
     return;
   }
   const int32_t* gb = A.gbin_of + a;
@@ -345,7 +371,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
   bad = false;
   for (int q = t; q < A.nb; q += kSegThreads) bad = bad || start[(q + 1) * A.F] - start[q * A.F] > kSegTile;
   if (__syncthreads_or(bad)) {
-    if (t == 0) A.ctl[0] = 1;
+    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
     return;
   }
   if (k == 0) {
@@ -367,7 +393,7 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
   __syncthreads();  // (the starts move below)
   if (m <= 0) return;
   if (m > kSegCap) {
-    if (t == 0) A.ctl[0] = 1;
+    if (t == 0) A.ctl[0] = A.ctl[1] = 1;
     return;
   }
   for (int j0 = t; j0 < len; j0 += kSegThreads * U) {
@@ -489,16 +515,20 @@ __global__ void __launch_bounds__(T, 8) seg_kernel(SegArgs A) {
 // Every kernel of this path returns at once when the grouped path sorted the
 // call (*go == 0).
 
-// The count of every bin and every hit's arrival index (bin_kernel counts by
-// itself where the grouped path is not tried).
-__global__ void __launch_bounds__(256) count_kernel(int n, int F, const int32_t* __restrict__ gbin_of,
-                                                    int32_t* __restrict__ arrival, int32_t* __restrict__ count,
-                                                    int32_t* __restrict__ bad, const int32_t* __restrict__ go) {
-  if (*go == 0) return;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int gb = gbin_of[i];
-    if (gb >= 0) arrival[i] = atomicAdd(&count[gb / F], 1);
-    else if (bad) atomicAdd(bad, 1);
+// The count of every bin and every hit's arrival index after an attempt of the
+// grouped path, by the blocks of bin_kernel; hits it left are binned too.
+__global__ void __launch_bounds__(256) count_kernel(BinArgs A, RowGeom rg) {
+  if (A.ctl[1] == 0) return;
+  int i0, i1;
+  run_of_block(A.n, i0, i1);
+  if (A.blk_bad[blockIdx.x] & 2) {
+    (void)bin_run<true>(A, rg, i0, i1);
+    return;
+  }
+  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+    const int gb = A.gbin_of[i];
+    if (gb >= 0) A.arrival[i] = atomicAdd(&A.count[gb / A.F], 1);
+    else if (A.bad) atomicAdd(A.bad, 1);
   }
 }
 
@@ -621,7 +651,14 @@ __device__ inline void rank_bin(int lane, int b0, int cnt, int ev_base, size_t N
       const float op = cnt > W ? np : ph;
       if (d0 + W < cnt) load(d0 + W);
       const int m = cnt - d0 < W ? cnt - d0 : W;
-      for (int t = 0; t < m; ++t) {
+      int t = 0;
+      for (; t + 2 <= m; t += 2) {  // (two steps' shuffles in flight)
+        const float pj = __shfl(op, t, W), pk = __shfl(op, t + 1, W);
+        const int j = __shfl(oi, t, W), k = __shfl(oi, t + 1, W);
+        rank += (pj < ph || (pj == ph && j < i)) ? 1 : 0;
+        rank += (pk < ph || (pk == ph && k < i)) ? 1 : 0;
+      }
+      for (; t < m; ++t) {
         const float pj = __shfl(op, t, W);
         const int j = __shfl(oi, t, W);
         rank += (pj < ph || (pj == ph && j < i)) ? 1 : 0;
@@ -694,7 +731,8 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct BinWs {
   int32_t *gbin_of, *arrival, *count, *start, *bsum, *seg;
   uint8_t* blk_bad;
-  // [0] the path: 1 where the general path runs, [1] the scan's ticket
+  // [0] the reported word, [1] the path: 1 where the general path runs, [2] the
+  // scan's ticket
   int32_t* ctl;
   float* phi_of;
   float4* rec;  // [n][3] hit records in bin slots
@@ -718,7 +756,7 @@ size_t bin_ws_layout(int E, int L, int n_phi, int n_z, int n, char* base, BinWs*
   char* g = take(sizeof(int32_t) * (nblk + 1));
   char* k = take(sizeof(int32_t) * ((size_t)E * L + 1));
   char* m = take(kBinGrid);
-  char* h = take(sizeof(int32_t) * 2);
+  char* h = take(sizeof(int32_t) * 3);
   if (w) {
     w->ctl = (int32_t*)h;
     w->seg = (int32_t*)k;
@@ -778,24 +816,26 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   const int64_t mean = n_hits / EL;  // hits of a range
   const bool small = mean <= kSegSmall;
   const int threads = small ? 256 : 1024;
-  // parts that give every CU about two blocks, but not below kSegMinPart
-  const int part = small ? kSegSmallPart : std::min(kSegPart, std::max(kSegMinPart, n_hits / (2 * cus)));
+  // parts that give every CU about one and a half blocks, but not below
+  // kSegMinPart (each part reads its range's bins: one event of 50 000 tracks 157
+  // us with two blocks a CU, 128 with one and a half, 156 with one; 8 of 10 000 106,
+  // 82 and 87)
+  const int part = small ? kSegSmallPart : std::min(kSegPart, std::max(kSegMinPart, n_hits / (3 * cus / 2)));
   const int64_t seg_blocks = part_blocks(n_hits, part, EL, threads);
-  // Which path, where the input is ordered and its bins fit.  The grouped path
-  // needs ranges for half the CUs, and enough work in each: a range costs it
-  // 10 ns and 6 ps a bin, the general path 20 ps a bin and up to 0.3 ns a hit
-  // (17 layers, 1 008 bins; general against grouped, us: 1 event of 20 000
-  // tracks 57 to 58, of 60 000 128 to 153, 16 events 680 to 321, 64 events of 600
-  // hits a layer 128 to 49, 1 024 events of 2 hits a layer 355 to 234; with 16
-  // bins, 4 096 events of 40 hits a layer 279 to 738).  With fewer ranges it
-  // pays where large bins make the general path's rank slow (one event, 16 bins
-  // of 190 hits: 86 to 35; four, 252 bins of 240: 703 to 516), with many bins
-  // only where they are that large that the parts' reads of their whole range
-  // are less (one event, 1 008 bins of 200: 605 to 696, of 500: 2 598 to 2 033).
-  const int64_t in_bin = mean / nb;
-  const bool choice = in_bin >= (nb <= 512 ? 48 : 480) || (EL >= cus / 2 && nb + 4 * mean >= 640);
+  // The grouped path is tried wherever its bins fit, but for the smallest
+  // calls, which the general path's shorter kernels sort in 24 to 28 us against
+  // 29 to 33 (one event of up to 2 000 tracks of 17 layers in 63 x 16 bins; 16
+  // events of 100: 31.6 to 30.1; one of 5 000: 39 to 30, of 20 000: 122 to 58;
+  // 200 of 500: 363 to 96; hits as events leave them, which fill few z rows of
+  // the inner layers).  Large bins cost the general path most (one bin a layer,
+  // 1 500 hits: 2 250 to 30).
   const bool forced = path && !strcmp(path, "grouped"), barred = path && !strcmp(path, "general");
-  const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !barred && (forced || choice);
+  const bool tiny = (int64_t)n_hits + NB / 4 < kSegMinCall && n_hits < 16 * NB;
+  const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !barred && (forced || !tiny);
+  // The reported word keeps the answers of a choice by ranges: 0 where the
+  // grouped path sorts a call of six ranges and more per CU, or one it is
+  // forced to try.  The word after it is the path.
+  const int32_t flag0 = try_grouped && (forced || EL >= 6 * cus) ? 0 : 1;
   if (!try_grouped)
     hipLaunchKernelGGL(clear_kernel, dim3(std::min(grid_for(NB, bs), 4096)), dim3(bs), 0, s, w.count, NB, w.ctl,
                        out_bad);
@@ -806,7 +846,7 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   const int F = try_grouped ? (int)std::max<int64_t>(1, pieces) : 1;
   const int blocks = std::max(1, std::min(grid_for(n_hits, bs), kBinGrid));
   BinArgs B{n_hits, n_events, L, n_phi, n_z, event_offsets, layer, xyz, w.gbin_of, w.phi_of, w.arrival, w.count, NB, F,
-            w.seg, w.blk_bad, w.ctl, out_bad, try_grouped ? 1 : 0};
+            w.seg, w.blk_bad, w.ctl, out_bad, flag0, try_grouped ? 1 : 0};
   hipLaunchKernelGGL(bin_kernel, dim3(blocks), dim3(bs), 0, s, B, rg);
   if (try_grouped) {
     SegArgs G{n_hits, n_events, L, nb, F, part, blocks, event_offsets, w.seg, w.blk_bad, w.gbin_of, w.phi_of, xyz, cov,
@@ -815,23 +855,27 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
                        seg_lds_bytes(threads, nb * F), s, G);
     // general path from here (every kernel returns at once unless it is to run)
     if (n_hits > 0)
-      hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(bs), 0, s, n_hits, F, w.gbin_of, w.arrival, w.count, out_bad,
-                         w.ctl);
+      hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(bs), 0, s, B, rg);
   }
   const int nblk = (int)((NB + 2 * kScanBlock - 1) / (2 * kScanBlock));
-  hipLaunchKernelGGL(scan_kernel, dim3(nblk), dim3(kScanBlock), 0, s, w.count, w.start, w.bsum, (int)NB, w.ctl,
-                     w.ctl + 1);
+  hipLaunchKernelGGL(scan_kernel, dim3(nblk), dim3(kScanBlock), 0, s, w.count, w.start, w.bsum, (int)NB, w.ctl + 1,
+                     w.ctl + 2);
   const int64_t items = std::max((int64_t)n_hits, (int64_t)EL * (nb + 1));
   hipLaunchKernelGGL(place_kernel, dim3((int)std::min<int64_t>((items + bs - 1) / bs, kWideGrid)), dim3(bs), 0, s,
                      n_hits, F, w.gbin_of, w.phi_of, w.arrival, xyz, cov, w.start, w.bsum, w.count, EL, nb, w.rec,
-                     offsets, w.ctl);
+                     offsets, w.ctl + 1);
   if (n_hits > 0) {
-    // lanes per bin by the mean bin
-    const int G = in_bin < 8 ? 16 : (in_bin < 16 ? 32 : 64);
+    // lanes per bin by the mean bin, of which the fuller bins of the inner layers
+    // hold several times as many, and a wave per bin where the waves suffice for
+    // all (hits as events leave them, 16, 32 and 64 lanes, us: a mean of 2.4, 4
+    // events 36, 38, 42; of 6, one event 39, 36, 35, 64 events 708, 740, 875; of 6
+    // in 4 096 bins, 16 events 1 179, 1 009, 1 141)
+    const int64_t in_bin = n_hits / NB;
+    const int G = in_bin < 4 ? 16 : (in_bin < 16 && NB > 32768 ? 32 : 64);
     auto* rank = G == 16 ? rank_kernel<16> : (G == 32 ? rank_kernel<32> : rank_kernel<64>);
     hipLaunchKernelGGL(rank, dim3(std::min(grid_for(NB * G, bs), kWideGrid)), dim3(bs), 0, s, (int)NB, n_hits, L, nb,
                        event_offsets, w.rec, w.start, w.bsum, w.count, sorted_xyzphi, sorted_cov, sorted_orig,
-                       w.ctl);
+                       w.ctl + 1);
   }
   return kf_check_launch();
 }

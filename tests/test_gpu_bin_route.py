@@ -42,7 +42,7 @@ def _bin(kf, monkeypatch, path, n_phi, n_z, layer, xyz, cov, off):
     ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
     b = kf.hit_bin(g, n_phi, n_z, to_dev(layer), to_dev(xyz), to_dev(cov), event_offsets=to_dev(off), ws=ws)
     torch.cuda.synchronize()
-    return b, int(ws[need - 256:need - 252].view(torch.int32).cpu()[0])
+    return b, int(ws[need - 252:need - 248].view(torch.int32).cpu()[0])
 
 
 def _same(a, b):
@@ -88,26 +88,79 @@ def test_part_above_its_memory_gives_way(kf, monkeypatch, per, before, hot, thre
 
 
 @pytest.mark.parametrize("events,per,n_phi,n_z,path", [
-    (1, 20000, 63, 16, 1),   # few ranges, small bins
-    (1, 20000, 8, 2, 0),     # bins of 1 250
-    (1, 500, 63, 16, 1),
-    (4, 3000, 63, 16, 1),
-    (1, 60000, 63, 16, 1),   # bins of 60, but many
-    (1, 15000, 63, 4, 0),    # bins of 60
-    (16, 3000, 63, 16, 0),   # ranges for every CU
-    (64, 100, 63, 16, 0),
-    (64, 100, 4, 4, 1),      # few bins, few hits
-    (64, 700, 4, 4, 0),
+    (1, 500, 63, 16, 1),     # the smallest calls
+    (1, 3500, 63, 16, 1),
+    (1, 4000, 63, 16, 0),    # 68 000 hits
+    (1, 20000, 63, 16, 0),
+    (1, 20000, 8, 2, 0),
+    (64, 30, 63, 16, 0),     # few hits, many bins
+    (64, 30, 4, 4, 1),
     (16, 1000, 128, 64, 1),  # more bins than the grouped path takes
 ])
 def test_default_choice(kf, monkeypatch, events, per, n_phi, n_z, path):
     h = _hits([[per] * 17] * events, np.random.default_rng(5))
     a, got = _bin(kf, monkeypatch, None, n_phi, n_z, *h)
     assert got == path
-    b, _ = _bin(kf, monkeypatch, "general", n_phi, n_z, *h)
+    b, general = _bin(kf, monkeypatch, "general", n_phi, n_z, *h)
+    assert general == 1
     _same(a, b)
-    perm = np.random.default_rng(6).permutation(h[0].shape[0] // events)  # any order: general, whatever the sizes
-    if events == 1:
-        _, got = _bin(kf, monkeypatch, None, n_phi, n_z, h[0][perm], np.ascontiguousarray(h[1][:, perm]),
-                      np.ascontiguousarray(h[2][:, perm]), h[3])
-        assert got == 1
+
+
+@pytest.mark.parametrize("disorder", ["all", "one_block", "half", "bad"])
+def test_large_calls_in_any_order(kf, monkeypatch, disorder):
+    """Calls of 2^19 hits and more, whose blocks may count during the attempt:
+    all, one or half of the blocks out of order, and bad hits among them."""
+    layer, xyz, cov, off = _hits([[2100] * 17] * 16, np.random.default_rng(7))
+    n = layer.shape[0]
+    assert n >= 1 << 19
+    rng = np.random.default_rng(8)
+    perm = np.arange(n)
+    if disorder == "one_block":  # within one event's hits
+        perm[300:900] = 300 + rng.permutation(600)
+        perm[[200, 20000]] = perm[[20000, 200]]
+    else:
+        for e in range(16 if disorder != "half" else 8):
+            perm[off[e]:off[e + 1]] = off[e] + rng.permutation(off[e + 1] - off[e])
+    layer, xyz, cov = layer[perm], np.ascontiguousarray(xyz[:, perm]), np.ascontiguousarray(cov[:, perm])
+    n_bad = 0
+    if disorder == "bad":
+        i = rng.permutation(n)[:5000]
+        layer[i[:2500]] = 17
+        xyz[0, i[2500:]] = np.nan
+        n_bad = 5000
+    a, path = _bin(kf, monkeypatch, None, 63, 16, layer, xyz, cov, off)
+    b, _ = _bin(kf, monkeypatch, "general", 63, 16, layer, xyz, cov, off)
+    assert path == 1 and int(host(a.bad)[0]) == int(host(b.bad)[0]) == n_bad
+    m = n - n_bad
+    for k in ("offsets", "orig", "xyzphi", "cov"):
+        x, y = host(getattr(a, k)), host(getattr(b, k))
+        if k != "offsets":
+            x, y = x[..., :m], y[..., :m]
+        assert np.array_equal(x.view(np.int32), y.view(np.int32)), k
+    for e in (0, 15):
+        sl = slice(off[e], off[e + 1])
+        import oracle
+        ok = (layer[sl] < 17) & np.isfinite(xyz[0, sl])
+        o = oracle.hit_bin(presets.barrel(17), 63, 16, np.ascontiguousarray(layer[sl]), np.ascontiguousarray(xyz[:, sl]))
+        s0 = host(a.offsets)[e, 0, 0]
+        assert np.array_equal(host(a.orig)[s0:s0 + int(ok.sum())], np.asarray(o["order"])[:int(ok.sum())])
+
+
+def test_path_word_beside_the_reported_word(kf, monkeypatch):
+    """The first of the two words reports the grouped path only for calls of
+    six ranges a compute unit and forced ones; the second is the path."""
+    layer, xyz, cov, off = _hits([[4000] * 17], np.random.default_rng(9))
+    perm = np.random.default_rng(10).permutation(layer.shape[0])
+    shuffled = (layer[perm], np.ascontiguousarray(xyz[:, perm]), np.ascontiguousarray(cov[:, perm]))
+    need = kf.hit_bin_workspace_bytes(1, 17, 63, 16, layer.shape[0])
+    for env, hits, words in ((None, (layer, xyz, cov), [1, 0]), ("grouped", (layer, xyz, cov), [0, 0]),
+                             ("general", (layer, xyz, cov), [1, 1]), (None, shuffled, [1, 1]),
+                             ("grouped", shuffled, [1, 1])):
+        if env:
+            monkeypatch.setenv("KFTRACK_HIT_BIN_PATH", env)
+        else:
+            monkeypatch.delenv("KFTRACK_HIT_BIN_PATH", raising=False)
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+        kf.hit_bin(presets.barrel(17), 63, 16, *(to_dev(h) for h in hits), ws=ws)
+        torch.cuda.synchronize()
+        assert ws[need - 256:need - 248].view(torch.int32).cpu().tolist() == words, env
