@@ -819,8 +819,10 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   // parts that give every CU about one and a half blocks, but not below
   // kSegMinPart (each part reads its range's bins: one event of 50 000 tracks 157
   // us with two blocks a CU, 128 with one and a half, 156 with one; 8 of 10 000 106,
-  // 82 and 87)
-  const int part = small ? kSegSmallPart : std::min(kSegPart, std::max(kSegMinPart, n_hits / (3 * cus / 2)));
+  // 82 and 87); two where the ranges alone fill the chip (64 of 2 000: 111 and 118)
+  // or the parts come near their largest (8 of 20 000: 186 and 192)
+  const int slots = EL >= 2 * cus || n_hits / (2 * cus) >= 5000 ? 2 * cus : 3 * cus / 2;
+  const int part = small ? kSegSmallPart : std::min(kSegPart, std::max(kSegMinPart, n_hits / slots));
   const int64_t seg_blocks = part_blocks(n_hits, part, EL, threads);
   // The grouped path is tried wherever its bins fit, but for the smallest
   // calls, which the general path's shorter kernels sort in 24 to 28 us against
@@ -831,7 +833,12 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   // 1 500 hits: 2 250 to 30).
   const bool forced = path && !strcmp(path, "grouped"), barred = path && !strcmp(path, "general");
   const bool tiny = (int64_t)n_hits + NB / 4 < kSegMinCall && n_hits < 16 * NB;
-  const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !barred && (forced || !tiny);
+  // Ranges of few bins and few hits cost a block each more than the general path
+  // its bins (765 000 ranges of 4 hits in 16 bins 7.5 ms to 1.2; 17 408 of 40 204 us
+  // to 70, of 150 228 to 227, of 600 435 to 846; of 10 in 252 bins 198 to 150, of 40
+  // 209 to 250).
+  const bool thin = nb + 4 * mean < 640;
+  const bool try_grouped = nb <= kSegMaxBins && seg_blocks > 0 && !barred && (forced || !(tiny || thin));
   // The reported word keeps the answers of a choice by ranges: 0 where the
   // grouped path sorts a call of six ranges and more per CU, or one it is
   // forced to try.  The word after it is the path.

@@ -95,6 +95,8 @@ def test_part_above_its_memory_gives_way(kf, monkeypatch, per, before, hot, thre
     (1, 20000, 8, 2, 0),
     (64, 30, 63, 16, 0),     # few hits, many bins
     (64, 30, 4, 4, 1),
+    (64, 100, 4, 4, 1),      # few hits, few bins
+    (64, 160, 4, 4, 0),
     (16, 1000, 128, 64, 1),  # more bins than the grouped path takes
 ])
 def test_default_choice(kf, monkeypatch, events, per, n_phi, n_z, path):
