@@ -125,10 +125,10 @@ __device__ inline void run_of_block(int n, int& i0, int& i1) {
   i1 = at + per < n ? (int)(at + per) : n;
 }
 
-// Bins the block's hits, and counts them (COUNT) or writes the range starts and
-// returns whether they are in order.
+// Bins the block's hits, and counts them (COUNT) or writes the range starts.
+// Returns the block's bits of blk_bad (of this thread's hits for bit 0).
 template <bool COUNT>
-__device__ inline bool bin_run(const BinArgs& A, const RowGeom& rg, int i0, int i1) {
+__device__ inline int bin_run(const BinArgs& A, const RowGeom& rg, int i0, int i1) {
   const int n = A.n, E = A.E, L = A.L, nb = A.n_phi * A.n_z, t = threadIdx.x;
   const int32_t* eoff = A.eoff;
   int elo = 0, ehi = 1;
@@ -150,6 +150,9 @@ __device__ inline bool bin_run(const BinArgs& A, const RowGeom& rg, int i0, int 
     zn = A.xyz[2 * (size_t)n + i];
   };
   load(t);
+  // (a descent of the layer starts an event in ordered input; the check runs
+  // behind the loads of the coordinates)
+  if (!COUNT && __syncthreads_count(t < i1 - i0 && ln < lpn) > 64) return 3;
   for (int k = t; k < i1 - i0; k += 256) {
     const int i = i0 + k;
     const int l = ln, lp = lpn;
@@ -174,7 +177,7 @@ __device__ inline bool bin_run(const BinArgs& A, const RowGeom& rg, int i0, int 
     if (COUNT) A.arrival[i] = atomicAdd(&A.count[gb], 1);
     else ok = range_starts(eoff, E, L, n, i, e, l, lp, A.seg) && ok;
   }
-  return ok;
+  return ok ? 0 : 1;
 }
 
 __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
@@ -185,9 +188,6 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
     (void)bin_run<true>(A, rg, i0, i1);
     return;
   }
-  // (a descent of the layer starts an event in ordered input; loaded first, the
-  // clearing below hides it)
-  const bool falls = t > 0 && t < i1 - i0 && A.layer[i0 + t] < A.layer[i0 + t - 1];
   if (blockIdx.x == 0 && t == 0) {
     A.ctl[0] = A.flag0;
     A.ctl[1] = 0;
@@ -197,17 +197,13 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + t; k < A.NB; k += (int64_t)gridDim.x * blockDim.x) A.count[k] = 0;
   if (n == 0)
     for (int k = blockIdx.x * blockDim.x + t; k <= EL; k += gridDim.x * blockDim.x) A.seg[k] = 0;
-  if (__syncthreads_count(falls) > 64) {
-    if (t == 0) A.blk_bad[blockIdx.x] = 3;
-    return;
-  }
   bool ok = true;
   if (A.eoff)
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + t; e < E; e += (int64_t)gridDim.x * blockDim.x)
       ok = ok && tiles(A.eoff, E, n, (int)e);
-  ok = bin_run<false>(A, rg, i0, i1) && ok;
-  const int all_ok = __syncthreads_and(ok);
-  if (t == 0) A.blk_bad[blockIdx.x] = all_ok ? 0 : 1;
+  const int bits = bin_run<false>(A, rg, i0, i1);
+  const int any_bad = __syncthreads_or(!ok || (bits & 1));
+  if (t == 0) A.blk_bad[blockIdx.x] = (any_bad ? 1 : 0) | (bits & 2);
 }
 
 // ---- Grouped path -----------------------------------------------------------
@@ -820,8 +816,9 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   // kSegMinPart (each part reads its range's bins: one event of 50 000 tracks 157
   // us with two blocks a CU, 128 with one and a half, 156 with one; 8 of 10 000 106,
   // 82 and 87); two where the ranges alone fill the chip (64 of 2 000: 111 and 118)
-  // or the parts come near their largest (8 of 20 000: 186 and 192)
-  const int slots = EL >= 2 * cus || n_hits / (2 * cus) >= 5000 ? 2 * cus : 3 * cus / 2;
+  // or the parts are near their largest (8 of 20 000: 186 and 192) or smallest
+  // (4 of 5 000: 46 and 49)
+  const int two = n_hits / (2 * cus), slots = EL >= 2 * cus || two >= 5000 || two < 900 ? 2 * cus : 3 * cus / 2;
   const int part = small ? kSegSmallPart : std::min(kSegPart, std::max(kSegMinPart, n_hits / slots));
   const int64_t seg_blocks = part_blocks(n_hits, part, EL, threads);
   // The grouped path is tried wherever its bins fit, but for the smallest
