@@ -235,7 +235,8 @@ __global__ void __launch_bounds__(256) bin_kernel(BinArgs A, RowGeom rg) {
 // 1 700 ranges of about 5 000 hits: 199 us here and 311 for the call, against
 // 616 with one block per range that scattered whole records to their bins in
 // memory and read them back (214 B a hit); 408 ranges of 20 000 in three
-// parts each: 400 us for the call, against 876 by the general path then.  A longer prefetch (18 loads a thread) changed nothing.
+// parts each: 400 us for the call, against 876 by the general path then.  A
+// longer prefetch (18 loads a thread) changed nothing.
 constexpr int kSegPer = 8;                       // positions of a part per thread, at most
 constexpr int kSegTile = 2048;                   // hits of a bin at most
 constexpr int kSegPart = 6784;                   // leaves room for the rest of a piece
@@ -686,9 +687,9 @@ __device__ inline void rank_bin(int lane, int b0, int cnt, int ev_base, size_t N
 // G lanes per bin, 64 / G bins at once; where one of these bins is so much
 // the largest that the others' lanes would mostly wait for it, all 64 lanes
 // take the bins one after another (85 000 shuffled hits, a bin of 1 000 a layer:
-// 5 239 us with G lanes alone, 1 003 so; 20 bins of 100 a layer: 122 and 72).
-// 8.16 M hits, 5 a bin: 500 us with 64 lanes a bin, 454 with 16; 20 a bin: 790
-// us with 32 lanes, 613 with 64.
+// 5 239 us with G lanes alone, 1 003 so; 20 bins of 100 a layer: 122 and 72).  A
+// call of 6.5 M hits, 6 a bin: 872 us with 64 lanes a bin, 719 with 16; 24 a bin:
+// 819 us with 32 lanes, 747 with 64.
 template <int G>
 __global__ void __launch_bounds__(256) rank_kernel(int NB, int n, int L, int nb_el,
                                                    const int32_t* __restrict__ eoff,
@@ -829,10 +830,10 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
   const int64_t seg_blocks = part_blocks(n_hits, part, EL, threads);
   // The grouped path is tried wherever its bins fit, but for the smallest
   // calls, which the general path's shorter kernels sort in 24 to 28 us against
-  // 29 to 33 (one event of up to 2 000 tracks of 17 layers in 63 x 16 bins; 16
-  // events of 100: 31.6 to 30.1; one of 5 000: 39 to 30, of 20 000: 122 to 58;
-  // 200 of 500: 363 to 96; hits as events leave them, which fill few z rows of
-  // the inner layers).  Large bins cost the general path most (one bin a layer,
+  // 29 to 34 (one event of up to 2 000 tracks of 17 layers in 63 x 16 bins; 16
+  // events of 100: 33 to 31; one of 5 000: 34 to 31, of 20 000: 108 to 60; 200 of
+  // 500: 363 to 99; hits as events leave them, which fill few z rows of the
+  // inner layers).  Large bins cost the general path most (one bin a layer,
   // 1 500 hits: 2 250 to 30).
   const bool forced = path && !strcmp(path, "grouped"), barred = path && !strcmp(path, "general");
   const bool tiny = (int64_t)n_hits + NB / 4 < kSegMinCall && n_hits < 16 * NB;
@@ -878,8 +879,9 @@ int run_hit_bin(int L, const RowGeom& rg, int32_t n_events, const int32_t* event
     // lanes per bin by the mean bin, of which the fuller bins of the inner layers
     // hold several times as many, and a wave per bin where the waves suffice for
     // all (hits as events leave them, 16, 32 and 64 lanes, us: a mean of 2.4, 4
-    // events 36, 38, 42; of 6, one event 39, 36, 35, 64 events 708, 740, 875; of 6
-    // in 4 096 bins, 16 events 1 179, 1 009, 1 141)
+    // events 38, 39, 44; of 6, one event 38, 34, 33, 64 events 719, 737, 872; of 12,
+    // 16 events 431, 374, 390; of 6 in 4 096 bins, 16 events 896, 915, 1 071, of
+    // 15, 8 events 1 594, 1 274, 1 311)
     const int64_t in_bin = n_hits / NB;
     const int G = in_bin < 4 ? 16 : (in_bin < 16 && NB > 32768 ? 32 : 64);
     auto* rank = G == 16 ? rank_kernel<16> : (G == 32 ? rank_kernel<32> : rank_kernel<64>);
